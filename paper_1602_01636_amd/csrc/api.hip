@@ -327,6 +327,9 @@ igafd_status upload_dir(const Dir1D& h, DevDir* d, hipStream_t st) {
   d->npad = fd_npad(h.n);
   igafd_status s;
   if ((s = dev_upload(&d->elem_first, h.elem_first.data(), h.elem_first.size(), st)) != IGAFD_OK) return s;
+  std::vector<int> at((size_t)h.n + 2, -1);
+  for (int e = 0; e < h.nel; ++e) at[h.elem_first[e]] = e;
+  if ((s = dev_upload(&d->elem_at, at.data(), at.size(), st)) != IGAFD_OK) return s;
   if ((s = dev_upload(&d->qx, h.qx.data(), h.qx.size(), st)) != IGAFD_OK) return s;
   if ((s = dev_upload(&d->qw, h.qw.data(), h.qw.size(), st)) != IGAFD_OK) return s;
   if ((s = dev_upload(&d->val, h.val.data(), h.val.size(), st)) != IGAFD_OK) return s;
@@ -374,6 +377,7 @@ igafd_status upload_dir(const Dir1D& h, DevDir* d, hipStream_t st) {
 
 void free_dir(DevDir* d) {
   free_dev(d->elem_first);
+  free_dev(d->elem_at);
   free_dev(d->qx);
   free_dev(d->qw);
   free_dev(d->val);
@@ -387,6 +391,19 @@ void free_dir(DevDir* d) {
   free_dev(d->diagM);
   free_dev(d->diagK);
   *d = DevDir{};
+}
+
+// the scratch allocation, cut into the given N-vectors (each 256-byte aligned)
+igafd_status alloc_scratch(igafd_ctx* c, std::initializer_list<double**> vecs) {
+  const long long nv = (c->N + 31) / 32 * 32;
+  c->scratch_len = std::max((long long)vecs.size() * nv, load_scratch(c));
+  IGAFD_HIP_CHECK(hipMalloc((void**)&c->scratch, sizeof(double) * (size_t)c->scratch_len));
+  double* p = c->scratch;
+  for (double** v : vecs) {
+    *v = p;
+    p += nv;
+  }
+  return IGAFD_OK;
 }
 
 // Preconditioner-only context of one Schwarz subdomain (2D): the univariate
@@ -406,7 +423,7 @@ igafd_status create_fd_sub(int p, const Dir1D& d1, const Dir1D& d2, hipStream_t 
     c->N *= c->n[l];
     if ((s = upload_dir(c->dir[l], &c->ddir[l], st)) != IGAFD_OK) return s;
   }
-  for (int b = 0; b < 2; ++b) IGAFD_HIP_CHECK(hipMalloc((void**)&c->fdbuf[b], sizeof(double) * (size_t)c->N));
+  if ((s = alloc_scratch(c.get(), {&c->fdbuf[0], &c->fdbuf[1]})) != IGAFD_OK) return s;
   *out = c.release();
   return IGAFD_OK;
 }
@@ -491,19 +508,14 @@ igafd_status parse_geometry(const igafd_problem* pr, GeomDesc* g) {
 }
 
 igafd_status alloc_workspace(igafd_ctx* c) {
-  const size_t vb = sizeof(double) * (size_t)c->N;
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->r, vb));
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->z, vb));
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->zold, vb));
+  const igafd_status s = alloc_scratch(c, {&c->r, &c->z, &c->zold, &c->q, &c->fdbuf[0], &c->fdbuf[1]});
+  if (s != IGAFD_OK) return s;
   const size_t pb = sizeof(double) * (size_t)c->Ns;
   IGAFD_HIP_CHECK(hipMalloc((void**)&c->pv_pad, pb));
   IGAFD_HIP_CHECK(hipMalloc((void**)&c->xpad, pb));
   IGAFD_HIP_CHECK(hipMemsetAsync(c->pv_pad, 0, pb, c->stream));
   IGAFD_HIP_CHECK(hipMemsetAsync(c->xpad, 0, pb, c->stream));
   c->pv = c->pv_pad + c->halo;
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->q, vb));
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->fdbuf[0], vb));
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->fdbuf[1], vb));
   // partial sums: one (or two) per block of every reduction kernel, for any
   // kernel shape the autotuner may pick
   c->npartial = partial_capacity(c);
@@ -1577,6 +1589,7 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
   }
   for (int l = 0; l < pr->dim; ++l)
     if ((s = upload_dir(c->dir[l], &c->ddir[l], c->stream)) != IGAFD_OK) return s;
+  if ((s = setup_modes(c.get())) != IGAFD_OK) return s;
   const int W = 2 * c->p + 1;
   const int Sz = (c->dim == 3) ? W * W * W : W * W;
   c->H = (Sz + 1) / 2;
@@ -1593,7 +1606,7 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
   if (!with_A) {
     // FD intermediates (FP64 is the widest) and the block partials of the
     // preconditioner's (r, s) product and of the spectral bounds
-    for (int b = 0; b < 2; ++b) IGAFD_HIP_CHECK(hipMalloc((void**)&c->fdbuf[b], sizeof(double) * (size_t)c->N));
+    if ((s = alloc_scratch(c.get(), {&c->fdbuf[0], &c->fdbuf[1]})) != IGAFD_OK) return s;
     c->npartial = partial_capacity(c.get());
     IGAFD_HIP_CHECK(hipMalloc((void**)&c->partial, sizeof(double) * 2 * (size_t)c->npartial));
     IGAFD_HIP_CHECK(hipStreamSynchronize(c->stream));
@@ -1664,14 +1677,9 @@ void igafd_destroy(igafd_ctx* c) {
   for (int l = 0; l < 3; ++l) free_dir(&c->ddir[l]);
   free_dev(c->band);
   free_dev(c->ext);
-  free_dev(c->r);
-  free_dev(c->z);
-  free_dev(c->zold);
+  free_dev(c->scratch);
   free_dev(c->pv_pad);
   free_dev(c->xpad);
-  free_dev(c->q);
-  free_dev(c->fdbuf[0]);
-  free_dev(c->fdbuf[1]);
   free_dev(c->scaling);
   free_dev(c->partial);
   free_dev(c->state);
@@ -1681,6 +1689,7 @@ void igafd_destroy(igafd_ctx* c) {
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   free_dev(c->hist);
   free_dev(c->feat);
+  free_dev(c->modes);
   for (hipEvent_t e : c->tev) (void)hipEventDestroy(e);
   delete c;
 }

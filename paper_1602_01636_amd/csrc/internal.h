@@ -70,6 +70,7 @@ igafd_status build_direction(int p, int q, int nknots, const double* knots, Dir1
 struct DevDir {
   int n = 1, nel = 1, npad = 32;
   int* elem_first = nullptr;
+  int* elem_at = nullptr;  // [n + 2]: element whose first function (boundary ones counted) is f, or -1
   double* qx = nullptr;
   double* qw = nullptr;
   double* val = nullptr;
@@ -140,7 +141,10 @@ struct igafd_ctx {
   int hole = -1;
   igafd_ctx* sub[2] = {nullptr, nullptr};
   igafd_adi* adi = nullptr;                // set: the preconditioner is P_J (three-variable ADI)
-  // workspace
+  // workspace: one allocation holding r, z, zold, q and the FD intermediates (the
+  // latter alone without A), between solves and applies scratch of load vectors
+  double* scratch = nullptr;
+  long long scratch_len = 0;
   double *r = nullptr, *z = nullptr, *q = nullptr, *zold = nullptr;
   double* pv_pad = nullptr;                // search direction with the band's zero halo
   double* pv = nullptr;                    // = pv_pad + halo
@@ -154,6 +158,7 @@ struct igafd_ctx {
   igafd::SolverState* hstate = nullptr;    // pinned host mirror
   int* dflag = nullptr;                    // device error flag (geometry)
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  double* modes = nullptr;                 // direction tables of a warped map's modes (assembly.hip)
   float* feat = nullptr;                   // per-dof features (N x 8) assembled with A, when asked for
   double* hist = nullptr;                  // device residual history of igafd_solve
   int hist_alloc = 0;                      // doubles allocated at hist
@@ -172,6 +177,8 @@ struct igafd_ctx {
 
 namespace igafd {
 // assembly.hip
+igafd_status setup_modes(igafd_ctx* c);
+long long load_scratch(const igafd_ctx* c);  // doubles that a load vector needs at least
 igafd_status assemble_band(igafd_ctx* c, bool with_features);
 igafd_status assemble_load(igafd_ctx* c, int rhs_kind, const double* params, int nparams, double* b);
 igafd_status diagonals(igafd_ctx* c, double* dA, double* dP);

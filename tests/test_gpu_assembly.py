@@ -1,0 +1,83 @@
+"""Assembly kernels (direction-by-direction sum factorisation) against the
+oracle's element loops, at the sizes where the walks and the runs can go wrong:
+runs of direction-1 functions that end on and next to a block's limit, several
+runs of planes, repeated knots up to multiplicity p (an element shift of more
+than one function), a single element per direction, padded and many map modes.
+
+Tolerances: A x and b are sums of products of about 10 rounded factors with a
+different summation order over at most (p+1)^3 (2p+1)^3 terms: a small multiple
+of eps times the sum of magnitudes, 1e-12.  Features are FP32 (2e-6)."""
+import numpy as np
+import pytest
+
+import synth
+from helpers import to_dev, to_host
+from oracle import assembly
+from oracle import mlp as omlp
+
+pytestmark = pytest.mark.gpu
+
+
+def _repeated(p, mults):
+    """Open knot vector with interior knots of the given multiplicities."""
+    E = len(mults) + 1
+    inner = [np.full(m, (k + 1) / E) for k, m in enumerate(mults)]
+    return np.concatenate([np.zeros(p + 1), *inner, np.ones(p + 1)])
+
+
+def _kappa():
+    return synth.sincos_coefficient(0.4, 1, 2, 0.3, 0.1)
+
+
+def cases():
+    u = synth.uniform_knots
+    warped = synth.warped_geometry
+    C = []
+    # direction-1 runs hold 63, 40, 29, 21, 16, 12 functions for p = 1..6
+    for p, e1 in ((1, 64), (1, 65), (2, 40), (2, 41), (3, 28), (3, 29), (4, 19), (4, 20), (5, 13), (5, 14), (6, 8), (6, 9)):
+        C.append((f"run_p{p}_E{e1}", synth.make_problem(3, p, [u(e1, p), u(3, p), u(2, p)], warped(p), _kappa())))
+    for p in range(1, 7):  # one element per direction (p = 1: two, the smallest with an interior function)
+        e = 2 if p == 1 else 1
+        C.append((f"one_element_p{p}", synth.make_problem(3, p, [u(e, p)] * 3, warped(p + 3), _kappa())))
+        C.append((f"2d_one_element_p{p}", synth.make_problem(2, p, [u(e, p)] * 2, warped(p + 3, dim=2), _kappa())))
+    C.append(("repeated_p3", synth.make_problem(3, 3, [_repeated(3, [1, 3, 2, 1]), _repeated(3, [3, 1]), _repeated(3, [2, 3])],
+                                                warped(2), _kappa())))
+    C.append(("repeated_2d_p4", synth.make_problem(2, 4, [_repeated(4, [4, 1, 2, 4]), _repeated(4, [1, 3, 4])],
+                                                   {"kind": "ring"}, _kappa())))
+    C.append(("planes_p2", synth.make_problem(3, 2, [u(4, 2), u(3, 2), synth.jittered_knots(40, 2, 3)], {"kind": "ring"})))
+    C.append(("modes_3", synth.make_problem(3, 2, [u(5, 2), u(4, 2), u(3, 2)], warped(4, modes=3), _kappa())))
+    C.append(("modes_16", synth.make_problem(3, 2, [u(5, 2), u(4, 2), u(3, 2)], warped(4, modes=16), _kappa())))
+    return C
+
+
+CASES = cases()
+
+
+@pytest.mark.parametrize("name,prob", CASES, ids=[c[0] for c in CASES])
+def test_assembly_matches_oracle(name, prob, rng):
+    import torch
+
+    import paper_1602_01636_amd as api
+    A = assembly.assemble_matrix(prob)
+    with api.igafd_setup(prob, features=True) as ctx:
+        N = ctx.N
+        assert N == A.shape[0]
+        x = rng.standard_normal(N)
+        y, dA, b = (to_dev(np.zeros(N)) for _ in range(3))
+        api.igafd_apply_A(ctx, to_dev(x), y)
+        assert np.max(np.abs(to_host(y) - A @ x) / (abs(A) @ np.abs(x))) < 1e-12
+        api.igafd_diagonals(ctx, dA)
+        np.testing.assert_allclose(to_host(dA), A.diagonal(), rtol=1e-12)
+        for rhs in (synth.RHS_SINPROD, synth.RHS_BUBBLE):
+            b.fill_(float("nan"))
+            api.igafd_load_vector(ctx, rhs, b)
+            ref = assembly.assemble_load(prob, rhs)
+            assert np.max(np.abs(to_host(b) - ref)) < 1e-12 * np.max(np.abs(ref))
+        feat = torch.full((8 * N,), float("nan"), dtype=torch.float32, device="cuda")
+        api.igafd_features(ctx, feat)
+        np.testing.assert_allclose(to_host(feat).reshape(-1, 8), omlp.features(prob), rtol=2e-6, atol=2e-7)
+    # a preconditioner-only context takes the load vector's scratch from fewer vectors
+    with api.igafd_setup_precond(prob) as pc:
+        b2 = to_dev(np.full(N, np.nan))
+        api.igafd_load_vector(pc, synth.RHS_BUBBLE, b2)
+        assert np.array_equal(to_host(b2), to_host(b))
