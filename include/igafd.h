@@ -27,7 +27,10 @@
  *    ABI.  igafd_last_error() gives a thread-local message for the last
  *    non-OK status.  A status > 0 is a warning with results written.
  *  - The context owns every device allocation it makes (matrix band,
- *    eigenvector copies, workspace); igafd_destroy frees them.
+ *    eigenvector copies, workspace); igafd_destroy releases them: blocks of
+ *    1 MiB or more to a cache of at most 8 GiB per device that later contexts
+ *    take them from (returned to the driver when unused for a while or when
+ *    an allocation fails), the others to the driver.
  */
 #ifndef IGAFD_H
 #define IGAFD_H

@@ -20,6 +20,9 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <system_error>
+#include <thread>
+#include <unordered_map>
 
 #include "internal.h"
 #include "reduce.h"
@@ -31,6 +34,106 @@ thread_local std::string g_err;
 }
 
 void set_error(const std::string& msg) { g_err = msg; }
+
+// Device blocks of 1 MiB or more, kept for the next context when one is
+// released.  Returning gigabytes to the driver and taking them again costs a
+// clear of that memory at about 33 GB/s once a process has cycled through its
+// cleared reserve (about 140 GB): 130 ms for the 4.3 GB band of a 112^3, p = 4
+// problem whose setup takes 20.  Bounds: kCacheBytes per device; a block is
+// reused for requests of at least 4/5 of its size, and given back to the
+// driver when kCacheAge later requests found no use for it, when the bound is
+// exceeded (oldest first), or when an allocation fails.  Callers release a
+// block only after the work that used it has finished.
+namespace {
+constexpr size_t kCacheMin = 1u << 20, kCacheBytes = (size_t)8 << 30;
+constexpr long long kCacheAge = 64;
+struct Block {
+  void* p;
+  size_t bytes;
+  int device;
+  long long stamp;
+};
+// (never destroyed: contexts may outlive the library's static objects)
+std::mutex& g_block_mutex = *new std::mutex;
+std::vector<Block>& g_cached = *new std::vector<Block>;                              // oldest first
+std::unordered_map<void*, Block>& g_blocks = *new std::unordered_map<void*, Block>;  // in use
+long long g_block_clock = 0;
+
+void trim_blocks(int device, size_t keep, long long oldest) {  // under the mutex
+  size_t held = 0;
+  for (const Block& b : g_cached) held += b.device == device ? b.bytes : 0;
+  for (size_t k = 0; k < g_cached.size();) {
+    const Block b = g_cached[k];
+    if ((b.device == device && held > keep) || b.stamp < oldest) {
+      (void)hipFree(b.p);
+      if (b.device == device) held -= b.bytes;
+      g_cached.erase(g_cached.begin() + (long)k);
+    } else {
+      ++k;
+    }
+  }
+}
+}  // namespace
+
+igafd_status block_alloc(void** p, size_t bytes) {
+  *p = nullptr;
+  int device = 0;
+  IGAFD_HIP_CHECK(hipGetDevice(&device));
+  if (bytes >= kCacheMin) {
+    std::lock_guard<std::mutex> lock(g_block_mutex);
+    g_block_clock += 1;
+    size_t best = g_cached.size();
+    for (size_t k = 0; k < g_cached.size(); ++k) {
+      const Block& b = g_cached[k];
+      if (b.device == device && b.bytes >= bytes && b.bytes - bytes <= bytes / 4 &&
+          (best == g_cached.size() || b.bytes < g_cached[best].bytes))
+        best = k;
+    }
+    if (best < g_cached.size()) {
+      const Block b = g_cached[best];
+      g_cached.erase(g_cached.begin() + (long)best);
+      g_blocks[b.p] = b;
+      *p = b.p;
+    }
+    trim_blocks(device, kCacheBytes, g_block_clock - kCacheAge);
+    if (*p) return IGAFD_OK;
+  }
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(g_block_mutex);
+    trim_blocks(device, 0, g_block_clock - kCacheAge);
+    e = hipMalloc(p, bytes);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+    set_error(std::string("device allocation of ") + std::to_string(bytes) + " bytes: " + hipGetErrorString(e));
+    return IGAFD_ERR_HIP;
+  }
+  if (bytes >= kCacheMin) {
+    std::lock_guard<std::mutex> lock(g_block_mutex);
+    g_blocks[*p] = Block{*p, bytes, device, 0};
+  }
+  return IGAFD_OK;
+}
+
+void block_free(void* p) {
+  if (!p) return;
+  {
+    std::lock_guard<std::mutex> lock(g_block_mutex);
+    const auto it = g_blocks.find(p);
+    if (it != g_blocks.end()) {
+      Block b = it->second;
+      g_blocks.erase(it);
+      b.stamp = g_block_clock;
+      g_cached.push_back(b);
+      trim_blocks(b.device, kCacheBytes, g_block_clock - kCacheAge);
+      return;
+    }
+  }
+  (void)hipFree(p);
+}
 
 // Block partials every reduction of a context may write (per sum): the
 // vector kernels' grid, every FD path and tile count, and at least 1025 (the
@@ -299,9 +402,7 @@ __global__ __launch_bounds__(kBlock) void k_residual(const double* __restrict__ 
   if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
-void free_dev(void* p) {
-  if (p) (void)hipFree(p);
-}
+void free_dev(void* p) { block_free(p); }
 
 unsigned vblocks(const igafd_ctx* c) { return (unsigned)((c->N + kBlock - 1) / kBlock); }
 
@@ -319,9 +420,8 @@ uint16_t to_bf16_host(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// Device copies of a direction: element tables, U^T and U in three
-// precisions (zero padded to npad x npad), eigenvalues, diagonals of M, K.
-igafd_status upload_dir(const Dir1D& h, DevDir* d, hipStream_t st) {
+// Device copies of a direction's element tables and the diagonals of M, K.
+igafd_status upload_tables(const Dir1D& h, DevDir* d, hipStream_t st) {
   d->n = h.n;
   d->nel = h.nel;
   d->npad = fd_npad(h.n);
@@ -334,18 +434,23 @@ igafd_status upload_dir(const Dir1D& h, DevDir* d, hipStream_t st) {
   if ((s = dev_upload(&d->qw, h.qw.data(), h.qw.size(), st)) != IGAFD_OK) return s;
   if ((s = dev_upload(&d->val, h.val.data(), h.val.size(), st)) != IGAFD_OK) return s;
   if ((s = dev_upload(&d->der, h.der.data(), h.der.size(), st)) != IGAFD_OK) return s;
-  const int n = h.n, np = d->npad;
-  if (h.U.empty()) {  // no eigendecomposition: element tables and diagonals only
-    std::vector<double> dm(n), dk(n);
-    for (int i = 0; i < n; ++i) {
-      dm[i] = h.M[(size_t)i * n + i];
-      dk[i] = h.K[(size_t)i * n + i];
-    }
-    if ((s = dev_upload(&d->diagM, dm.data(), dm.size(), st)) != IGAFD_OK) return s;
-    if ((s = dev_upload(&d->diagK, dk.data(), dk.size(), st)) != IGAFD_OK) return s;
-    IGAFD_HIP_CHECK(hipStreamSynchronize(st));
-    return IGAFD_OK;
+  const int n = h.n;
+  std::vector<double> dm(n), dk(n);
+  for (int i = 0; i < n; ++i) {
+    dm[i] = h.M[(size_t)i * n + i];
+    dk[i] = h.K[(size_t)i * n + i];
   }
+  if ((s = dev_upload(&d->diagM, dm.data(), dm.size(), st)) != IGAFD_OK) return s;
+  if ((s = dev_upload(&d->diagK, dk.data(), dk.size(), st)) != IGAFD_OK) return s;
+  IGAFD_HIP_CHECK(hipStreamSynchronize(st));  // the host copies must outlive the asynchronous uploads
+  return IGAFD_OK;
+}
+
+// Device copies of its eigenvalues, U^T and U in three precisions (zero padded
+// to npad x npad).
+igafd_status upload_eigen(const Dir1D& h, DevDir* d, hipStream_t st) {
+  const int n = h.n, np = d->npad;
+  igafd_status s;
   if ((s = dev_upload(&d->lam, h.lam.data(), h.lam.size(), st)) != IGAFD_OK) return s;
   std::vector<double> w64((size_t)np * np);
   std::vector<float> w32((size_t)np * np);
@@ -363,15 +468,41 @@ igafd_status upload_dir(const Dir1D& h, DevDir* d, hipStream_t st) {
     if ((s = dev_upload(&d->Wbf[which], wbf.data(), wbf.size(), st)) != IGAFD_OK) return s;
     IGAFD_HIP_CHECK(hipStreamSynchronize(st));  // host staging vectors are reused
   }
-  std::vector<double> dm(n), dk(n);
-  for (int i = 0; i < n; ++i) {
-    dm[i] = h.M[(size_t)i * n + i];
-    dk[i] = h.K[(size_t)i * n + i];
+  return IGAFD_OK;
+}
+
+// The eigendecompositions of the given directions: equal ones (same degree and
+// knots) once, the others on a thread each.
+igafd_status eigen_all(const std::vector<Dir1D*>& dirs) {
+  std::vector<int> same(dirs.size());
+  std::vector<igafd_status> st(dirs.size(), IGAFD_OK);
+  std::vector<std::thread> th;
+  for (size_t i = 0; i < dirs.size(); ++i) {
+    same[i] = (int)i;
+    for (size_t j = 0; j < i && same[i] == (int)i; ++j)
+      if (dirs[j]->p == dirs[i]->p && dirs[j]->q == dirs[i]->q && dirs[j]->knots == dirs[i]->knots) same[i] = (int)j;
   }
-  if ((s = dev_upload(&d->diagM, dm.data(), dm.size(), st)) != IGAFD_OK) return s;
-  if ((s = dev_upload(&d->diagK, dk.data(), dk.size(), st)) != IGAFD_OK) return s;
-  // the host copies must outlive the asynchronous uploads
-  IGAFD_HIP_CHECK(hipStreamSynchronize(st));
+  auto run = [&](size_t i) { st[i] = eigen_direction(dirs[i]); };
+  for (size_t i = 1; i < dirs.size(); ++i) {
+    if (same[i] != (int)i) continue;
+    try {
+      th.emplace_back(run, i);
+    } catch (const std::system_error&) {  // no thread to be had
+      run(i);
+    }
+  }
+  run(0);
+  for (std::thread& t : th) t.join();
+  for (size_t i = 0; i < dirs.size(); ++i) {
+    if (st[i] != IGAFD_OK) {
+      set_error("Cholesky of the 1D mass matrix failed");
+      return st[i];
+    }
+    if (same[i] != (int)i) {
+      dirs[i]->U = dirs[same[i]]->U;
+      dirs[i]->lam = dirs[same[i]]->lam;
+    }
+  }
   return IGAFD_OK;
 }
 
@@ -397,7 +528,10 @@ void free_dir(DevDir* d) {
 igafd_status alloc_scratch(igafd_ctx* c, std::initializer_list<double**> vecs) {
   const long long nv = (c->N + 31) / 32 * 32;
   c->scratch_len = std::max((long long)vecs.size() * nv, load_scratch(c));
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->scratch, sizeof(double) * (size_t)c->scratch_len));
+  const size_t bytes = sizeof(double) * (size_t)c->scratch_len;
+  const igafd_status s = block_alloc((void**)&c->scratch, bytes);
+  if (s != IGAFD_OK) return s;
+  IGAFD_HIP_CHECK(hipMemsetAsync(c->scratch, 0, bytes, c->stream));
   double* p = c->scratch;
   for (double** v : vecs) {
     *v = p;
@@ -421,7 +555,8 @@ igafd_status create_fd_sub(int p, const Dir1D& d1, const Dir1D& d2, hipStream_t 
   for (int l = 0; l < 2; ++l) {
     c->n[l] = c->dir[l].n;
     c->N *= c->n[l];
-    if ((s = upload_dir(c->dir[l], &c->ddir[l], st)) != IGAFD_OK) return s;
+    if ((s = upload_tables(c->dir[l], &c->ddir[l], st)) != IGAFD_OK) return s;
+    if ((s = upload_eigen(c->dir[l], &c->ddir[l], st)) != IGAFD_OK) return s;
   }
   if ((s = alloc_scratch(c.get(), {&c->fdbuf[0], &c->fdbuf[1]})) != IGAFD_OK) return s;
   *out = c.release();
@@ -508,11 +643,11 @@ igafd_status parse_geometry(const igafd_problem* pr, GeomDesc* g) {
 }
 
 igafd_status alloc_workspace(igafd_ctx* c) {
-  const igafd_status s = alloc_scratch(c, {&c->r, &c->z, &c->zold, &c->q, &c->fdbuf[0], &c->fdbuf[1]});
+  igafd_status s = alloc_scratch(c, {&c->r, &c->z, &c->zold, &c->q, &c->fdbuf[0], &c->fdbuf[1]});
   if (s != IGAFD_OK) return s;
   const size_t pb = sizeof(double) * (size_t)c->Ns;
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->pv_pad, pb));
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->xpad, pb));
+  if ((s = block_alloc((void**)&c->pv_pad, pb)) != IGAFD_OK) return s;
+  if ((s = block_alloc((void**)&c->xpad, pb)) != IGAFD_OK) return s;
   IGAFD_HIP_CHECK(hipMemsetAsync(c->pv_pad, 0, pb, c->stream));
   IGAFD_HIP_CHECK(hipMemsetAsync(c->xpad, 0, pb, c->stream));
   c->pv = c->pv_pad + c->halo;
@@ -1583,13 +1718,22 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
   if ((s = parse_geometry(pr, &c->geom)) != IGAFD_OK) return s;
   c->N = 1;
   for (int l = 0; l < pr->dim; ++l) {
-    if ((s = build_direction(pr->degree, q, pr->nknots[l], pr->knots[l], &c->dir[l], fd)) != IGAFD_OK) return s;
+    if ((s = build_direction(pr->degree, q, pr->nknots[l], pr->knots[l], &c->dir[l], false)) != IGAFD_OK) return s;
     c->n[l] = c->dir[l].n;
     c->N *= c->n[l];
   }
   for (int l = 0; l < pr->dim; ++l)
-    if ((s = upload_dir(c->dir[l], &c->ddir[l], c->stream)) != IGAFD_OK) return s;
-  if ((s = setup_modes(c.get())) != IGAFD_OK) return s;
+    if ((s = upload_tables(c->dir[l], &c->ddir[l], c->stream)) != IGAFD_OK) return s;
+  // the univariate eigendecompositions and their copies (host)
+  auto eigen = [&]() -> igafd_status {
+    if (!fd) return IGAFD_OK;
+    std::vector<Dir1D*> d;
+    for (int l = 0; l < pr->dim; ++l) d.push_back(&c->dir[l]);
+    igafd_status e = eigen_all(d);
+    for (int l = 0; l < pr->dim && e == IGAFD_OK; ++l) e = upload_eigen(c->dir[l], &c->ddir[l], c->stream);
+    return e;
+  };
+  if (with_A && c->dim == 3 && pr->want_features && (s = setup_modes(c.get())) != IGAFD_OK) return s;
   const int W = 2 * c->p + 1;
   const int Sz = (c->dim == 3) ? W * W * W : W * W;
   c->H = (Sz + 1) / 2;
@@ -1609,12 +1753,13 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
     if ((s = alloc_scratch(c.get(), {&c->fdbuf[0], &c->fdbuf[1]})) != IGAFD_OK) return s;
     c->npartial = partial_capacity(c.get());
     IGAFD_HIP_CHECK(hipMalloc((void**)&c->partial, sizeof(double) * 2 * (size_t)c->npartial));
+    if ((s = eigen()) != IGAFD_OK) return s;
     IGAFD_HIP_CHECK(hipStreamSynchronize(c->stream));
     c->t_setup_ms = elapsed_ms(t_start);
     *out = c.release();
     return IGAFD_OK;
   }
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->band, sizeof(double) * (size_t)c->H * (size_t)c->Ns));
+  if ((s = block_alloc((void**)&c->band, sizeof(double) * (size_t)c->H * (size_t)c->Ns)) != IGAFD_OK) return s;
   if ((s = alloc_workspace(c.get())) != IGAFD_OK) return s;
   {
     // 3D: tiled A product by default (IGAFD_SPMV_TILE=0 selects the row-parallel
@@ -1642,8 +1787,12 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
     }
     if ((s = spmv_set_tile(c.get(), b2, b3, tb)) != IGAFD_OK) return s;
   }
-  if ((s = assemble_band(c.get(), pr->want_features != 0)) != IGAFD_OK) return s;
-  IGAFD_HIP_CHECK(hipStreamSynchronize(c->stream));
+  // the device assembles A while the host computes the eigendecompositions
+  AsmWork work{nullptr, c->stream};
+  s = assemble_band(c.get(), pr->want_features != 0, &work);
+  const igafd_status se = s == IGAFD_OK ? eigen() : s;
+  if (se != IGAFD_OK) return se;
+  if ((s = assemble_finish(c.get())) != IGAFD_OK) return s;
   c->t_setup_ms = elapsed_ms(t_start);
   *out = c.release();
   return IGAFD_OK;
@@ -1671,7 +1820,7 @@ igafd_status igafd_univariate(int degree, int nknots, const double* knots, int q
 
 void igafd_destroy(igafd_ctx* c) {
   if (!c) return;
-  if (c->stream) (void)hipStreamSynchronize(c->stream);
+  (void)hipStreamSynchronize(c->stream);  // its blocks may go to another context and stream
   for (int k = 0; k < 2; ++k) igafd_destroy(c->sub[k]);
   adi_free(c);
   for (int l = 0; l < 3; ++l) free_dir(&c->ddir[l]);
@@ -1713,7 +1862,7 @@ igafd_status igafd_lshape_setup(int degree, int nknots, const double* knots, voi
   const int p = degree;
   Dir1D patch;
   igafd_status s;
-  if ((s = build_direction(p, p + 1, nknots, knots, &patch)) != IGAFD_OK) return s;
+  if ((s = build_direction(p, p + 1, nknots, knots, &patch, false)) != IGAFD_OK) return s;
   // the knot vector of two patches side by side: the patch knots on [0,1/2]
   // and on [1/2,1], joined by a knot of multiplicity p at 1/2 (C^0)
   std::vector<double> km;
@@ -1742,7 +1891,8 @@ igafd_status igafd_lshape_setup(int degree, int nknots, const double* knots, voi
   // direction 1, two along direction 2; Theta_2 = the corner patch and the one
   // to its right
   Dir1D merged;
-  if ((s = build_direction(p, p + 1, (int)km.size(), km.data(), &merged)) != IGAFD_OK) return s;
+  if ((s = build_direction(p, p + 1, (int)km.size(), km.data(), &merged, false)) != IGAFD_OK) return s;
+  if ((s = eigen_all({&patch, &merged})) != IGAFD_OK) return s;
   if ((s = create_fd_sub(p, patch, merged, c->stream, &c->sub[0])) != IGAFD_OK) return s;
   if ((s = create_fd_sub(p, merged, patch, c->stream, &c->sub[1])) != IGAFD_OK) return s;
   c->hole = h;
@@ -1873,7 +2023,7 @@ igafd_status igafd_set_scaling(igafd_ctx* c, const double* S) {
     return IGAFD_OK;
   }
   if (is_lshape(c, "the scaled preconditioner")) return IGAFD_ERR_ARG;
-  if (!c->scaling) IGAFD_HIP_CHECK(hipMalloc((void**)&c->scaling, sizeof(double) * c->N));
+  if (!c->scaling && block_alloc((void**)&c->scaling, sizeof(double) * c->N) != IGAFD_OK) return IGAFD_ERR_HIP;
   IGAFD_HIP_CHECK(hipMemcpyAsync(c->scaling, S, sizeof(double) * c->N, hipMemcpyDeviceToDevice, c->stream));
   c->scaling_set = true;
   return IGAFD_OK;
@@ -1984,7 +2134,7 @@ igafd_status igafd_set_scaling_diag_ratio(igafd_ctx* c) {
   }
   if (is_lshape(c, "the scaled preconditioner")) return IGAFD_ERR_ARG;
   if (no_A(c, "igafd_set_scaling_diag_ratio")) return IGAFD_ERR_ARG;
-  if (!c->scaling) IGAFD_HIP_CHECK(hipMalloc((void**)&c->scaling, sizeof(double) * c->N));
+  if (!c->scaling && block_alloc((void**)&c->scaling, sizeof(double) * c->N) != IGAFD_OK) return IGAFD_ERR_HIP;
   igafd_status st = diag_ratio_scaling(c, c->scaling);
   if (st == IGAFD_OK) c->scaling_set = true;
   return st;

@@ -2,9 +2,14 @@
 //
 // Paper Sec. 2.1 eq. A / eq. Q: A_ij = int_[0,1]^d grad(B_i)^T Q grad(B_j) with
 // Q = |det J| J^-1 K J^-T (J_ij = dF_i/dxi_j), by the tensor (p+1)-point Gauss
-// rule on every element.  The sums over the Gauss points are taken one
-// direction at a time over the whole domain (sum factorisation across the
-// elements, not element by element):
+// rule on every element.  Only the upper half of the stencil is stored: plane h
+// holds offset center + h of the (2p+1)^d stencil, indexed by the row.
+//
+// Element by element (k_assemble, k_load): one workgroup per element, local
+// matrix by sum factorisation, added into the band in (p+1)^d colour classes.
+//
+// Across the elements (3D contexts that keep the learned-scaling features):
+// the Gauss sums are taken one direction at a time over the whole domain.
 //   1. k_contract3: a thread owns one column of Gauss points (q1, q2), walks
 //      q3, evaluates C = w Q (Q = kappa adj(J) adj(J)^T / |det J|, no inverse)
 //      and contracts it with the pairs of direction-3 functions,
@@ -14,14 +19,16 @@
 // The contraction of a direction walks the functions in order: an element adds
 // to the pairs of its p+1 functions, held in registers, and the pairs of the
 // first of them are complete when the walk leaves it.  Every entry is written
-// by one thread, once, in a fixed summation order (bitwise reproducible, no
-// atomics, no read of the band).
-// Only the upper half of the stencil is stored: plane h holds offset
-// center + h of the (2p+1)^d stencil, indexed by the row.
+// by one thread, once.  Features and load vectors go the same way.
 // Measured, warped cube with kappa: 112^3, p = 4: 15.1 ms for the band (4.3 GB)
-// where element-by-element assembly in (p+1)^3 colours, reading and adding
-// to the band, took 197 ms; load vector 2.9 ms (22.6 ms by colours); 16^3, p = 3:
-// 42 us in 2 launches (1.7 ms in 64).  2D annulus 1024^2, p = 3: 0.41 ms (2.9 ms).
+// against 197 ms by colours (which read, add to and write it); load vector 2.9
+// against 22.6 ms; 16^3, p = 3: 42 us in 2 launches against 1.7 ms in 64.
+//
+// Both sums are in a fixed order (bitwise reproducible, no atomics), but not in
+// the same one: the entries differ in their last bits.  Contexts without the
+// features keep the element order because flexible CG with plain BF16 applies
+// turns a last bit of A or b into up to 3e-9 of the solution (the applies round
+// to 8 bits, and the iterates take another path within the same tolerance).
 #include <algorithm>
 
 #include "internal.h"
@@ -189,6 +196,169 @@ __device__ void feature_sums(int ch0, const double* vals, const double (*sV)[P +
   __syncthreads();
 }
 
+// FEAT = 1: also the per-dof feature sums of the learned scaling into acc
+// (8 doubles per dof), from the same Gauss-point evaluation of the map.
+template <int D, int P, int FEAT>
+__global__ __launch_bounds__(kBlock, (D == 3 && P <= 4) ? 5 : 1) void k_assemble(Tables T, GeomDesc g, double* __restrict__ band,
+                                                     long long Ns, int c1, int c2, int c3, int m1, int m2,
+                                                     int* __restrict__ err, double* __restrict__ acc) {
+  constexpr int Q = P + 1, L = P + 1;
+  constexpr int Q3 = (D == 3) ? Q : 1;
+  constexpr int L3 = (D == 3) ? L : 1;
+  constexpr int NQ = Q * Q * Q3;
+  constexpr int NC = (D == 3) ? 6 : 3;
+  constexpr int NAB = D * D;
+  constexpr int W = 2 * P + 1;
+  constexpr int S = (D == 3) ? W * W * W : W * W;
+  constexpr int CENTER = (S - 1) / 2;
+  constexpr int R3 = (D == 3) ? P : 0;
+
+  __shared__ double sC[NC][NQ];
+  __shared__ double sV[3][Q][L];
+  __shared__ double sD[3][Q][L];
+  __shared__ double sH[NAB][Q * Q];
+  __shared__ double sG[NAB][L * L][Q];
+  __shared__ int sFirst[3];
+  // features: kappa and the weight per point, F2 of the contraction (F1 lives in sG)
+  __shared__ double sKap[FEAT ? NQ : 1], sW[FEAT ? NQ : 1];
+  // feature channels per pass: all eight, or four at a time from p = 5 on
+  // (eight made the LDS of p = 5 allow three blocks per CU instead of four)
+  constexpr int NCH = (P >= 5) ? 4 : 8;
+  __shared__ double sF2[FEAT ? NCH * L * L * Q3 : 1];  // the channel values, then F2
+  static_assert(!FEAT || NAB * L * L * Q >= NCH * L * Q * Q3, "feature scratch F1 must fit in sG");
+  static_assert(!FEAT || L * L * Q3 >= NQ, "channel values must fit in sF2");
+
+  int bid = blockIdx.x;
+  const int j1 = bid % m1;
+  bid /= m1;
+  const int j2 = bid % m2;
+  const int j3 = bid / m2;
+  const int e[3] = {c1 + j1 * (P + 1), c2 + j2 * (P + 1), (D == 3) ? c3 + j3 * (P + 1) : 0};
+  const int tid = threadIdx.x;
+
+  for (int idx = tid; idx < 3 * Q * L; idx += kBlock) {
+    const int l = idx / (Q * L), t = (idx / L) % Q, a = idx % L;
+    if (l < D) {
+      sV[l][t][a] = T.val[l][(e[l] * Q + t) * L + a];
+      sD[l][t][a] = T.der[l][(e[l] * Q + t) * L + a];
+    } else {
+      sV[l][t][a] = (t == 0 && a == 0) ? 1.0 : 0.0;
+      sD[l][t][a] = 0.0;
+    }
+  }
+  if (tid < 3) sFirst[tid] = (tid < D) ? T.first[tid][e[tid]] : 1;
+
+  for (int t = tid; t < NQ; t += kBlock) {
+    const int t1 = t % Q, t2 = (t / Q) % Q, t3 = t / (Q * Q);
+    double xi[3] = {T.qx[0][e[0] * Q + t1], T.qx[1][e[1] * Q + t2], 0.0};
+    double w = T.qw[0][e[0] * Q + t1] * T.qw[1][e[1] * Q + t2];
+    if (D == 3) {
+      xi[2] = T.qx[2][e[2] * Q + t3];
+      w *= T.qw[2][e[2] * Q + t3];
+    }
+    double x[3], J[3][3], A[3][3];
+    map_eval<D>(g, xi, x, J);
+    const double det = adjugate<D>(J, A);
+    if (!(det > 0.0)) *err = 1;
+    const double kap = kappa_eval(g, x);
+    const double f = w * kap / fabs(det);
+    for (int a = 0; a < D; ++a)
+      for (int b = a; b < D; ++b) {
+        double s = 0.0;
+        for (int k = 0; k < D; ++k) s += A[a][k] * A[b][k];
+        sC[sym_index<D>(a, b)][t] = f * s;
+      }
+    if (FEAT) {
+      sKap[t] = kap;
+      sW[t] = w;
+    }
+  }
+  __syncthreads();
+  if (FEAT) {
+    // the channel values at the Gauss points, once each per pass: w G_ab =
+    // C_ab / kappa; the channel order is (11, 22, 33, 12, 13, 23, kappa, 1)
+    for (int ch0 = 0; ch0 < 8; ch0 += NCH) {
+      for (int idx = tid; idx < NCH * NQ; idx += kBlock) {
+        const int ch = ch0 + idx / NQ, t = idx % NQ;
+        constexpr int ia[6] = {0, 1, 2, 0, 0, 1}, ib[6] = {0, 1, 2, 1, 2, 2};
+        double v;
+        if (ch == 6)
+          v = sW[t] * sKap[t];
+        else if (ch == 7)
+          v = sW[t];
+        else if (ia[ch] >= D || ib[ch] >= D)
+          v = 0.0;
+        else
+          v = sC[sym_index<D>(ia[ch], ib[ch])][t] / sKap[t];
+        sF2[idx] = v;
+      }
+      __syncthreads();
+      feature_sums<D, P, NCH>(ch0, sF2, sV, sFirst, T, &sG[0][0][0], sF2, acc);
+    }
+  }
+
+  for (int a3 = 0; a3 < L3; ++a3) {
+    for (int b3 = a3; b3 < L3; ++b3) {
+      // H[ab][t1 + Q t2] = sum_t3 C_ab(t) phi3(a3) phi3(b3)
+      for (int idx = tid; idx < NAB * Q * Q; idx += kBlock) {
+        const int ab = idx / (Q * Q), t12 = idx % (Q * Q);
+        const int a = ab / D, b = ab % D;
+        const int ci = sym_index<D>(a, b);
+        double s = 0.0;
+#pragma unroll
+        for (int t3 = 0; t3 < Q3; ++t3) {
+          const double fa = (a == 2) ? sD[2][t3][a3] : sV[2][t3][a3];
+          const double fb = (b == 2) ? sD[2][t3][b3] : sV[2][t3][b3];
+          s += sC[ci][t12 + Q * Q * t3] * fa * fb;
+        }
+        sH[ab][t12] = s;
+      }
+      __syncthreads();
+      // G[ab][a2 + L b2][t1] = sum_t2 H[ab][t1 + Q t2] phi2(a2) phi2(b2)
+      for (int idx = tid; idx < NAB * L * L * Q; idx += kBlock) {
+        const int ab = idx / (L * L * Q), rem = idx % (L * L * Q);
+        const int a2b2 = rem / Q, t1 = rem % Q;
+        const int a2 = a2b2 % L, b2 = a2b2 / L;
+        const int a = ab / D, b = ab % D;
+        double s = 0.0;
+#pragma unroll
+        for (int t2 = 0; t2 < Q; ++t2) {
+          const double fa = (a == 1) ? sD[1][t2][a2] : sV[1][t2][a2];
+          const double fb = (b == 1) ? sD[1][t2][b2] : sV[1][t2][b2];
+          s += sH[ab][t1 + Q * t2] * fa * fb;
+        }
+        sG[ab][a2b2][t1] = s;
+      }
+      __syncthreads();
+      // local entry (a1 a2 a3 | b1 b2 b3) = sum_ab sum_t1 G phi1(a1) phi1(b1)
+      for (int idx = tid; idx < L * L * L * L; idx += kBlock) {
+        const int a1 = idx % L, b1 = (idx / L) % L, a2 = (idx / (L * L)) % L, b2 = idx / (L * L * L);
+        const int o1 = b1 - a1, o2 = b2 - a2, o3 = b3 - a3;
+        if (o3 == 0 && (o2 < 0 || (o2 == 0 && o1 < 0))) continue;  // lower half: not stored
+        const int r1 = sFirst[0] + a1 - 1, r2 = sFirst[1] + a2 - 1, r3 = (D == 3) ? sFirst[2] + a3 - 1 : 0;
+        const int q1 = r1 + o1, q2 = r2 + o2, q3 = r3 + o3;
+        if (r1 < 0 || r1 >= T.n[0] || r2 < 0 || r2 >= T.n[1] || r3 < 0 || r3 >= T.n[2]) continue;
+        if (q1 < 0 || q1 >= T.n[0] || q2 < 0 || q2 >= T.n[1] || q3 < 0 || q3 >= T.n[2]) continue;
+        double s = 0.0;
+#pragma unroll
+        for (int ab = 0; ab < NAB; ++ab) {
+          const int a = ab / D, b = ab % D;
+#pragma unroll
+          for (int t1 = 0; t1 < Q; ++t1) {
+            const double fa = (a == 0) ? sD[0][t1][a1] : sV[0][t1][a1];
+            const double fb = (b == 0) ? sD[0][t1][b1] : sV[0][t1][b1];
+            s += sG[ab][a2 + L * b2][t1] * fa * fb;
+          }
+        }
+        const int oidx = ((o3 + R3) * W + (o2 + P)) * W + (o1 + P);
+        const long long row = r1 + (long long)T.n[0] * (r2 + (long long)T.n[1] * r3);
+        band[(long long)(oidx - CENTER) * Ns + row] += s;
+      }
+      __syncthreads();
+    }
+  }
+}
+
 // ---- columns of Gauss points ----
 // The map on the column (xi1, xi2) of Gauss points: x = base + xi3 e3 + sum_k
 // (a c_k sin(pi m_k3 xi3)) m0_k and the Jacobian alike, with the products
@@ -200,7 +370,7 @@ constexpr int kModePad = 4;  // the modes are padded (zero amplitude) to chunks 
 
 struct Modes {
   const double* d12[2];  // [q][K][2]: sin(pi m xi), pi m cos(pi m xi) of directions 1 and 2
-  const double* d3;      // [q][K][6]: a c_x s, a c_y s, a c_z s, a c_x s', a c_y s', a c_z s' (2D: s = 1, s' = 0)
+  const double* d3;      // [q][K][6]: a c_x s, a c_y s, a c_z s, a c_x s', a c_y s', a c_z s'
   int K;                 // modes, padded to a multiple of kModePad (0: none)
 };
 
@@ -279,7 +449,6 @@ __device__ inline void column_eval(const Column& c, int K, ctab_t* d3, const dou
 }
 
 // tables of Modes: one thread per (point, mode) of the three directions
-template <int D>
 __global__ void k_mode_tables(const double* qx0, const double* qx1, const double* qx2, int nq0, int nq1, int nq2,
                               GeomDesc g, int K, double* d0, double* d1, double* d3) {
   int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -291,7 +460,7 @@ __global__ void k_mode_tables(const double* qx0, const double* qx1, const double
     }
     const int q = i / K, k = i % K;
     double s = k < g.nmodes ? 1.0 : 0.0, ds = 0.0;
-    if (l < D && k < g.nmodes) {
+    if (k < g.nmodes) {
       double sn, co;
       sincos(M_PI * g.m[k][l] * (l == 0 ? qx0 : l == 1 ? qx1 : qx2)[q], &sn, &co);
       s = sn;
@@ -378,9 +547,8 @@ __device__ inline double rhs_eval(const RhsDesc& f, const double x[3]) {
 
 // Fields of the direction-3 contraction H (per pair (i3, i3 + o), o >= 0, and
 // Gauss column): 0..3 = C11 B B, C12 B B, C22 B B, C33 B' B'; 4, 5 = C13 B B',
-// C13 B' B; 6, 7 = C23 B B', C23 B' B (first factor: function i3).  2D: the
-// three values C11, C12, C22 themselves.
-constexpr int kFields3 = 8, kFields2 = 3;
+// C13 B' B; 6, 7 = C23 B B', C23 B' B (first factor: function i3).
+constexpr int kFields3 = 8;
 constexpr int kFeat = 7;
 
 // Direction-3 contraction.  A block owns kCol columns (q1, q2) and a run of
@@ -554,30 +722,7 @@ __global__ __launch_bounds__(kCol) void k_moment3(
   }
 }
 
-// 2D: the values at the Gauss points (VAL_C: C11, C12, C22; VAL_FEAT: the channels)
-template <int WHAT>
-__global__ __launch_bounds__(kCol) void k_points2(Tables T, GeomDesc g, Modes md, int nq1, int nq2,
-                                                  double* __restrict__ H, int* __restrict__ err) {
-  extern __shared__ double sm[];
-  const long long nq12 = (long long)nq1 * nq2;
-  const long long q12 = (long long)blockIdx.x * kCol + threadIdx.x;
-  if (q12 >= nq12) return;
-  const int q1 = (int)(q12 % nq1), q2 = (int)(q12 / nq1);
-  const Column col = column_of(g, T.qx[0][q1], T.qx[1][q2]);
-  column_modes(md, q1, q2, sm, threadIdx.x);
-  double x[3], J[3][3], v[7];
-  column_eval(col, md.K, (ctab_t*)md.d3, sm, threadIdx.x, 0, 0.0, x, J);
-  const double det = point_values<WHAT>(g, x, J, T.qw[0][q1] * T.qw[1][q2], v);
-  if (!(det > 0.0)) *err = 1;
-  if (WHAT == VAL_C) {
-    for (int j = 0; j < kFields2; ++j) H[j * nq12 + q12] = v[j];
-  } else {
-    v[2] = v[4] = v[5] = 0.0;  // no third direction
-    for (int j = 0; j < kFeat; ++j) H[j * nq12 + q12] = v[j];
-  }
-}
-
-// Runs of direction-1 functions of k_contract12 and k_load: 128 lanes cover
+// Runs of direction-1 functions of k_contract12: 128 lanes cover
 // the Gauss points of kRunElems elements, so of that many functions less p.
 template <int P>
 struct Run1 {
@@ -635,25 +780,25 @@ __device__ inline double wave_up1(double v) {
 // its elements from LDS took 10.6 ms (14 LDS reads per 14 FMAs); loading the next
 // element's fields ahead gained nothing at p <= 4 and spilled at p = 5 (1343
 // against 845 us per run of 72^3).
-template <int D, int P>
+template <int P>
 __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract12(
     Tables T, cidx_t* at, ctab_t* val, ctab_t* der, const double* __restrict__ H, double* __restrict__ band, long long Ns, int nq1, int nq2, int base, int len1,
     int len2) {
   extern __shared__ double sm[];
   using R = Run1<P>;
-  constexpr int Q = R::Q, W = 2 * P + 1, NF = D == 3 ? kFields3 : kFields2;
-  constexpr int CENTER = D == 3 ? (W * W * W - 1) / 2 : (W * W - 1) / 2;
-  constexpr int FX = D == 3 ? 5 : 2;              // fields read by the first half (the second: three, or one)
+  constexpr int Q = R::Q, W = 2 * P + 1, NF = kFields3;
+  constexpr int CENTER = (W * W * W - 1) / 2;
+  constexpr int FX = 5;                           // fields read by the first half (the second: three)
   constexpr int LPW = 64 / R::ELEMS;              // lines per wave in direction 1
   double* sG = sm;                                          // [4][W][QS]
   d2_t* sT = reinterpret_cast<d2_t*>(sm + 4 * W * R::QS);   // [ELEMS][TS]
   const int tid = threadIdx.x;
   const int half = tid / kCol, q = tid % kCol;
-  const int n1 = T.n[0], n2 = T.n[1], n3 = D == 3 ? T.n[2] : 1;
+  const int n1 = T.n[0], n2 = T.n[1], n3 = T.n[2];
   const int s0 = (int)blockIdx.x * len1, s1 = min(s0 + len1, n1);
   const int g0 = (int)blockIdx.z * len2, g1 = min(g0 + len2, n2);
   const int pair = (int)blockIdx.y;
-  const int o3 = D == 3 ? pair % (P + 1) : 0, i3 = D == 3 ? base + pair / (P + 1) : 0;
+  const int o3 = pair % (P + 1), i3 = base + pair / (P + 1);
   if (s0 >= s1 || g0 >= g1) return;
   const bool in3 = i3 + o3 < n3;
   const int elo = first_elem(T.at[0], s0 + 1, P), ehi = last_elem(T.at[0], s1);
@@ -680,7 +825,7 @@ __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract12(
   for (int a = 0; a <= P; ++a)
 #pragma unroll
     for (int b = 0; b <= P; ++b) ga[a][b] = gb[a][b] = 0.0;
-  // fields of the first half: 11, 32, 33, 22, 23; of the second: 31, 12, 13 and zeros (2D: 11, 22 | 12)
+  // fields of the first half: 11, 32, 33, 22, 23; of the second: 31, 12, 13 and zeros
   const long long off[3] = {half == 0 ? 0 : 5 * nq12, half == 0 ? 7 * nq12 : nq12, half == 0 ? 3 * nq12 : 4 * nq12};
   double hq[Q][FX];
 #pragma unroll
@@ -689,16 +834,11 @@ __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract12(
     for (int k = 0; k < FX; ++k) hq[t][k] = 0.0;
   auto load = [&](int e, int t, double (&h)[FX]) {
     const double* __restrict__ p = Hc + ((long long)e * Q + t) * nq1;
-    if constexpr (D == 3) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) h[k] = p[off[k]];
-      if (half == 0) {
-        h[3] = p[2 * nq12];
-        h[4] = p[6 * nq12];
-      }
-    } else {
-      h[0] = p[half == 0 ? 0 : nq12];
-      if (half == 0) h[1] = p[2 * nq12];
+    for (int k = 0; k < 3; ++k) h[k] = p[off[k]];
+    if (half == 0) {
+      h[3] = p[2 * nq12];
+      h[4] = p[6 * nq12];
     }
   };
   for (int f = g0 + 1 - P; f <= g1; ++f) {
@@ -712,25 +852,15 @@ __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract12(
         ctab_t* B = val + ((long long)e * Q + t) * Q;
         ctab_t* Bd = der + ((long long)e * Q + t) * Q;
         // ga: G_11 | G_01, gb: G_00 | G_10; the terms a half does not have are zero
-        const double h12 = half == 0 ? 0.0 : D == 3 ? h[1] : h[0];
+        const double h12 = half == 0 ? 0.0 : h[1];
 #pragma unroll
         for (int a = 0; a <= P; ++a) {
-          if constexpr (D == 3) {
-            const double u = fma(h12, Bd[a], h[0] * B[a]);
-            const double ud = fma(h[3], Bd[a], h[1] * B[a]), ub = fma(h[4], Bd[a], h[2] * B[a]);
+          const double u = fma(h12, Bd[a], h[0] * B[a]);
+          const double ud = fma(h[3], Bd[a], h[1] * B[a]), ub = fma(h[4], Bd[a], h[2] * B[a]);
 #pragma unroll
-            for (int b = 0; b <= P; ++b) {
-              ga[a][b] = fma(u, B[b], ga[a][b]);
-              gb[a][b] = fma(ud, Bd[b], fma(ub, B[b], gb[a][b]));
-            }
-          } else {
-            const double u = half == 0 ? h[0] * B[a] : h12 * Bd[a];
-            const double ud = fma(h[1], Bd[a], h12 * B[a]);
-#pragma unroll
-            for (int b = 0; b <= P; ++b) {
-              ga[a][b] = fma(u, B[b], ga[a][b]);
-              gb[a][b] = fma(ud, Bd[b], gb[a][b]);
-            }
+          for (int b = 0; b <= P; ++b) {
+            ga[a][b] = fma(u, B[b], ga[a][b]);
+            gb[a][b] = fma(ud, Bd[b], fma(ub, B[b], gb[a][b]));
           }
         }
       }
@@ -804,7 +934,7 @@ __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract12(
       }
       if (!mine || j < P) continue;
       double* __restrict__ row = band + i1 + (long long)n1 * (i2 + (long long)n2 * i3);
-      const int p0 = ((o3 + (D == 3 ? P : 0)) * W + l) * W - CENTER;
+      const int p0 = ((o3 + P) * W + l) * W - CENTER;
 #pragma unroll
       for (int o = 0; o < W; ++o) {
         const int j1 = i1 + o - P;
@@ -866,7 +996,7 @@ __device__ inline double moment1(const Tables& T, int l, int i) {
 // Moments, direction 1, for the planes i3 of [base, end), one thread per dof:
 // b_i (NCH = 1), or the features feat_i = (M_ch / M_w, p) in FP32, the moment
 // of w a product of univariate ones.
-template <int P, int NCH, int D, typename Out>
+template <int P, int NCH, typename Out>
 __global__ __launch_bounds__(kBlock) void k_moment1(Tables T, const double* __restrict__ M2, int nq1, int base,
                                                     int end, Out* __restrict__ out) {
   constexpr int Q = P + 1;
@@ -895,7 +1025,7 @@ __global__ __launch_bounds__(kBlock) void k_moment1(Tables T, const double* __re
   if constexpr (NCH == 1) {
     out[row] = s[0];
   } else {
-    const double den = moment1<P>(T, 0, i1) * moment1<P>(T, 1, i2) * (D == 3 ? moment1<P>(T, 2, base + i3) : 1.0);
+    const double den = moment1<P>(T, 0, i1) * moment1<P>(T, 1, i2) * moment1<P>(T, 2, base + i3);
     const double inv = 1.0 / den;
     typedef float f4_t __attribute__((ext_vector_type(4)));
     f4_t* o = reinterpret_cast<f4_t*>(out + 8 * row);
@@ -904,66 +1034,52 @@ __global__ __launch_bounds__(kBlock) void k_moment1(Tables T, const double* __re
   }
 }
 
-// 2D load vector b_i = sum_t w_t |det J| f(F(t)) B_i(t).  Block (x: run of
-// functions i1, z: run of functions i2): lane q holds a Gauss column q1 and
-// walks q2 with the direction-2 sums of the element's p+1 functions in
-// registers; a finished line goes to LDS and the block contracts direction 1.
-template <int P>
-__global__ __launch_bounds__(kCol) void k_load2(Tables T, GeomDesc g, Modes md, RhsDesc rhs, double* __restrict__ b,
-                                                int len1, int len2) {
-  extern __shared__ double sm[];
-  using R = Run1<P>;
-  constexpr int Q = R::Q;
-  double* sL = sm;            // [QS]
-  double* sM = sm + R::QS;    // [K][3][kCol]
+// b_i += sum_t w_t |det J| f(F(t)) B_i(t) over one colour class of elements.
+template <int D, int P>
+__global__ __launch_bounds__(kBlock) void k_load(Tables T, GeomDesc g, RhsDesc rhs, double* __restrict__ b,
+                                                 int c1, int c2, int c3, int m1, int m2) {
+  constexpr int Q = P + 1, L = P + 1;
+  constexpr int Q3 = (D == 3) ? Q : 1;
+  constexpr int L3 = (D == 3) ? L : 1;
+  constexpr int NQ = Q * Q * Q3;
+  __shared__ double sg[NQ];
+  __shared__ double sV[3][Q][L];
+  int bid = blockIdx.x;
+  const int j1 = bid % m1;
+  bid /= m1;
+  const int j2 = bid % m2;
+  const int j3 = bid / m2;
+  const int e[3] = {c1 + j1 * (P + 1), c2 + j2 * (P + 1), (D == 3) ? c3 + j3 * (P + 1) : 0};
   const int tid = threadIdx.x;
-  const int n1 = T.n[0], n2 = T.n[1];
-  const int s0 = (int)blockIdx.x * len1, s1 = min(s0 + len1, n1);
-  const int g0 = (int)blockIdx.z * len2, g1 = min(g0 + len2, n2);
-  if (s0 >= s1 || g0 >= g1) return;
-  const int elo = first_elem(T.at[0], s0 + 1, P), ehi = last_elem(T.at[0], s1);
-  const bool live = tid < (ehi - elo + 1) * Q;
-  const int q1 = elo * Q + (live ? tid : 0);
-  const int slot = (tid / Q) * R::QP + tid % Q;
-  double acc[P + 1];
-#pragma unroll
-  for (int a = 0; a <= P; ++a) acc[a] = 0.0;
-  for (int f = max(0, g0 + 1 - P); f <= g1; ++f) {
-    const int e = T.at[1][f];
-    if (e >= 0 && live) {
-#pragma unroll 1
-      for (int t = 0; t < Q; ++t) {
-        const int q2 = e * Q + t;
-        const Column col = column_of(g, T.qx[0][q1], T.qx[1][q2]);
-        column_modes(md, q1, q2, sM, tid);
-        double x[3], J[3][3], A[3][3];
-        column_eval(col, md.K, (ctab_t*)md.d3, sM, tid, 0, 0.0, x, J);
-        const double v = T.qw[0][q1] * T.qw[1][q2] * fabs(adjugate<3>(J, A)) * rhs_eval<2>(rhs, x);
-#pragma unroll
-        for (int a = 0; a <= P; ++a) acc[a] = fma(v, T.val[1][(long long)q2 * Q + a], acc[a]);
-      }
+  for (int idx = tid; idx < 3 * Q * L; idx += kBlock) {
+    const int l = idx / (Q * L), t = (idx / L) % Q, a = idx % L;
+    sV[l][t][a] = (l < D) ? T.val[l][(e[l] * Q + t) * L + a] : ((t == 0 && a == 0) ? 1.0 : 0.0);
+  }
+  for (int t = tid; t < NQ; t += kBlock) {
+    const int t1 = t % Q, t2 = (t / Q) % Q, t3 = t / (Q * Q);
+    double xi[3] = {T.qx[0][e[0] * Q + t1], T.qx[1][e[1] * Q + t2], 0.0};
+    double w = T.qw[0][e[0] * Q + t1] * T.qw[1][e[1] * Q + t2];
+    if (D == 3) {
+      xi[2] = T.qx[2][e[2] * Q + t3];
+      w *= T.qw[2][e[2] * Q + t3];
     }
-    if (f > g0) {
-      __syncthreads();  // the previous line has been read
-      if (live) sL[slot] = acc[0];
-      __syncthreads();
-      const int i1 = s0 + tid;
-      if (i1 < s1) {
-        double s = 0.0;
-#pragma unroll
-        for (int a = 0; a <= P; ++a) {
-          const int e1 = i1 + 1 - a >= 0 ? T.at[0][i1 + 1 - a] : -1;
-          if (e1 < 0) continue;
-#pragma unroll
-          for (int t = 0; t < Q; ++t)
-            s = fma(T.val[0][((long long)e1 * Q + t) * Q + a], sL[(e1 - elo) * R::QP + t], s);
-        }
-        b[i1 + (long long)n1 * (f - 1)] = s;
-      }
+    double x[3], J[3][3], A[3][3];
+    map_eval<D>(g, xi, x, J);
+    const double det = adjugate<D>(J, A);
+    sg[t] = w * fabs(det) * rhs_eval<D>(rhs, x);
+  }
+  __syncthreads();
+  for (int idx = tid; idx < L * L * L3; idx += kBlock) {
+    const int a1 = idx % L, a2 = (idx / L) % L, a3 = idx / (L * L);
+    const int r1 = T.first[0][e[0]] + a1 - 1, r2 = T.first[1][e[1]] + a2 - 1;
+    const int r3 = (D == 3) ? T.first[2][e[2]] + a3 - 1 : 0;
+    if (r1 < 0 || r1 >= T.n[0] || r2 < 0 || r2 >= T.n[1] || r3 < 0 || r3 >= T.n[2]) continue;
+    double s = 0.0;
+    for (int t = 0; t < NQ; ++t) {
+      const int t1 = t % Q, t2 = (t / Q) % Q, t3 = t / (Q * Q);
+      s += sg[t] * sV[0][t1][a1] * sV[1][t2][a2] * sV[2][t3][a3];
     }
-#pragma unroll
-    for (int a = 0; a < P; ++a) acc[a] = acc[a + 1];
-    acc[P] = 0.0;
+    b[r1 + (long long)T.n[0] * (r2 + (long long)T.n[1] * r3)] += s;
   }
 }
 
@@ -1212,138 +1328,175 @@ size_t mode_lds(const Modes& md) { return sizeof(double) * 3 * (size_t)md.K * kC
 int column_run(int count, int colb) { return std::min(count, std::max(2, cdiv((long long)count * colb, kAsmBlocks))); }
 
 // moments of directions 2 and 1 for the planes [base, end): M1 -> M2 -> out
-template <int D, int P, int NCH, typename Out>
+template <int P, int NCH, typename Out>
 igafd_status moments21(igafd_ctx* c, const Tables& T, const double* M1, double* M2, int base, int end, Out* out) {
   const int nq1 = c->dir[0].nel * (P + 1), nq2 = c->dir[1].nel * (P + 1), n2 = c->n[1];
   const int planes = (end - base) * NCH, qb = cdiv(nq1, kCol);
   const int len2 = std::min(n2, std::max(4, cdiv(n2, cdiv(kAsmBlocks, (long long)qb * planes))));
   hipLaunchKernelGGL((k_moment2<P>), dim3((unsigned)qb, (unsigned)planes, (unsigned)cdiv(n2, len2)), dim3(kCol), 0,
                      c->stream, T, (cidx_t*)T.at[1], (ctab_t*)T.val[1], M1, M2, nq1, nq2, len2);
-  hipLaunchKernelGGL((k_moment1<P, NCH, D, Out>), dim3((unsigned)cdiv((long long)c->n[0] * n2 * (end - base), kBlock)),
+  hipLaunchKernelGGL((k_moment1<P, NCH, Out>), dim3((unsigned)cdiv((long long)c->n[0] * n2 * (end - base), kBlock)),
                      dim3(kBlock), 0, c->stream, T, M2, nq1, base, end, out);
   IGAFD_HIP_CHECK(hipGetLastError());
   return IGAFD_OK;
 }
 
-// Assembly of the band (and the features) through a workspace of direction-3
+// Assembly of the band and the features across the elements, through a workspace of direction-3
 // contractions for a run of planes i3 at a time: every further run repeats the
 // evaluation of p element layers, so the run is as long as half the band's own
 // bytes (at most kAsmWorkMax) allow; it is halved when that much memory is not
 // there, down to one plane.
-template <int D, int P>
-igafd_status launch_assemble(igafd_ctx* c, bool with_features) {
+template <int P>
+igafd_status launch_across(igafd_ctx* c, AsmWork* work) {
   using R = Run1<P>;
-  constexpr int W = 2 * P + 1, NP3 = D == 3 ? P + 1 : 1, NF = D == 3 ? kFields3 : kFields2;
+  constexpr int W = 2 * P + 1, NP3 = P + 1, NF = kFields3;
   const Tables T = make_tables(c);
   const int nq1 = c->dir[0].nel * R::Q, nq2 = c->dir[1].nel * R::Q;
-  const int n2 = c->n[1], n3 = D == 3 ? c->n[2] : 1;
+  const int n2 = c->n[1], n3 = c->n[2];
   const long long nq12 = (long long)nq1 * nq2;
-  const long long layer = std::max((long long)NP3 * NF * nq12, with_features ? kFeat * (nq12 + (long long)n2 * nq1) : 0);
+  const long long layer = std::max((long long)NP3 * NF * nq12, kFeat * (nq12 + (long long)n2 * nq1));
   const long long cap = std::min(kAsmWorkMax, (long long)sizeof(double) * c->H * c->Ns / 2);
   int run = (int)std::max(1LL, std::min((long long)n3, cap / (layer * (long long)sizeof(double))));
   run = cdiv(n3, cdiv(n3, run));
-  double* ws = nullptr;
-  while (hipMalloc((void**)&ws, sizeof(double) * (size_t)run * (size_t)layer) != hipSuccess) {
-    (void)hipGetLastError();
-    if (run == 1) {
-      set_error("allocation of the assembly workspace failed");
-      return IGAFD_ERR_ALLOC;
-    }
+  igafd_status st;
+  while ((st = block_alloc((void**)&work->ws, sizeof(double) * (size_t)run * (size_t)layer)) != IGAFD_OK) {
+    if (run == 1) return st;
     run = (run + 1) / 2;
   }
-  struct Release {  // the launches that read the workspace are waited for
-    double* p;
-    hipStream_t st;
-    ~Release() {
-      (void)hipStreamSynchronize(st);
-      (void)hipFree(p);
-    }
-  } release{ws, c->stream};
+  double* ws = work->ws;
+  // the zero halo of every plane; the rows in between are all written below
+  const size_t pitch = sizeof(double) * (size_t)c->Ns;
+  const long long tail = c->halo + c->N;
+  IGAFD_HIP_CHECK(hipMemset2DAsync(c->band, pitch, 0, sizeof(double) * (size_t)c->halo, c->H, c->stream));
+  IGAFD_HIP_CHECK(
+      hipMemset2DAsync(c->band + tail, pitch, 0, sizeof(double) * (size_t)(c->Ns - tail), c->H, c->stream));
   const Modes md = modes_of(c);
   const size_t col_lds = mode_lds(md), lds3 = col_lds + sizeof(double) * 24 * kCol;
   const int colb = cdiv(nq12, kCol);
   const size_t lds = sizeof(double) * (4 * W * R::QS + 2 * R::ELEMS * R::TS);
   IGAFD_HIP_CHECK(
-      hipFuncSetAttribute((const void*)k_contract12<D, P>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  if constexpr (D == 3)
-    IGAFD_HIP_CHECK(
-        hipFuncSetAttribute((const void*)k_contract3<P>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds3));
+      hipFuncSetAttribute((const void*)k_contract12<P>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  IGAFD_HIP_CHECK(
+      hipFuncSetAttribute((const void*)k_contract3<P>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds3));
   const int runs1 = R::runs(c->n[0]), len1 = R::len(c->n[0]);
   for (int base = 0; base < n3; base += run) {
     const int end = std::min(n3, base + run);
-    if constexpr (D == 3) {
-      const int len = column_run(end - base, colb);
-      hipLaunchKernelGGL((k_contract3<P>), dim3((unsigned)colb, (unsigned)cdiv(end - base, len)), dim3(2 * kCol), lds3,
-                         c->stream, T, c->geom, md, nq1, nq2, (cidx_t*)T.at[2], (ctab_t*)T.qx[2],
-                         (ctab_t*)T.qw[2], (ctab_t*)T.val[2], (ctab_t*)T.der[2], (ctab_t*)md.d3, base, end,
-                         len, ws, c->dflag);
-    } else {
-      hipLaunchKernelGGL(k_points2<VAL_C>, dim3((unsigned)colb), dim3(kCol), col_lds, c->stream, T, c->geom, md, nq1,
-                         nq2, ws, c->dflag);
-    }
+    const int len = column_run(end - base, colb);
+    hipLaunchKernelGGL((k_contract3<P>), dim3((unsigned)colb, (unsigned)cdiv(end - base, len)), dim3(2 * kCol), lds3,
+                       c->stream, T, c->geom, md, nq1, nq2, (cidx_t*)T.at[2], (ctab_t*)T.qx[2],
+                       (ctab_t*)T.qw[2], (ctab_t*)T.val[2], (ctab_t*)T.der[2], (ctab_t*)md.d3, base, end,
+                       len, ws, c->dflag);
     IGAFD_HIP_CHECK(hipGetLastError());
     const int pairs = (end - base) * NP3;
     const int len2 = std::min(n2, std::max(4, cdiv(n2, cdiv(kAsmBlocks / 2, (long long)runs1 * pairs))));
-    hipLaunchKernelGGL((k_contract12<D, P>), dim3((unsigned)runs1, (unsigned)pairs, (unsigned)cdiv(n2, len2)),
+    hipLaunchKernelGGL((k_contract12<P>), dim3((unsigned)runs1, (unsigned)pairs, (unsigned)cdiv(n2, len2)),
                        dim3(2 * kCol), lds, c->stream, T, (cidx_t*)T.at[1], (ctab_t*)T.val[1], (ctab_t*)T.der[1], ws, c->band + c->halo, c->Ns, nq1, nq2, base, len1, len2);
     IGAFD_HIP_CHECK(hipGetLastError());
   }
-  if (!with_features) return IGAFD_OK;
   for (int base = 0; base < n3; base += run) {
     const int end = std::min(n3, base + run);
-    if constexpr (D == 3) {
-      const int len = column_run(end - base, colb);
-      hipLaunchKernelGGL((k_moment3<P, kFeat>), dim3((unsigned)colb, (unsigned)cdiv(end - base, len)), dim3(kCol),
-                         col_lds, c->stream, T, c->geom, md, RhsDesc{}, nq1, nq2, (cidx_t*)T.at[2], (ctab_t*)T.qx[2],
-                         (ctab_t*)T.qw[2], (ctab_t*)T.val[2], (ctab_t*)md.d3,
-                         base, end, len, ws);
-    } else {
-      hipLaunchKernelGGL(k_points2<VAL_FEAT>, dim3((unsigned)colb), dim3(kCol), col_lds, c->stream, T, c->geom, md,
-                         nq1, nq2, ws, c->dflag);
-    }
+    const int len = column_run(end - base, colb);
+    hipLaunchKernelGGL((k_moment3<P, kFeat>), dim3((unsigned)colb, (unsigned)cdiv(end - base, len)), dim3(kCol),
+                       col_lds, c->stream, T, c->geom, md, RhsDesc{}, nq1, nq2, (cidx_t*)T.at[2], (ctab_t*)T.qx[2],
+                       (ctab_t*)T.qw[2], (ctab_t*)T.val[2], (ctab_t*)md.d3,
+                       base, end, len, ws);
     IGAFD_HIP_CHECK(hipGetLastError());
-    const igafd_status st =
-        moments21<D, P, kFeat>(c, T, ws, ws + (long long)(end - base) * kFeat * nq12, base, end, c->feat);
+    st = moments21<P, kFeat>(c, T, ws, ws + (long long)(end - base) * kFeat * nq12, base, end, c->feat);
     if (st != IGAFD_OK) return st;
   }
   return IGAFD_OK;
 }
 
-// Load vector: 3D through the moments of a run of planes i3 at a time, held in
-// the context's CG (or FD) vectors; nothing is allocated.
-template <int D, int P>
-igafd_status launch_load(igafd_ctx* c, RhsDesc rhs, double* b) {
+// Load vector across the elements, through the moments of a run of planes i3 at
+// a time, held in the context's CG vectors; nothing is allocated.
+template <int P>
+igafd_status load_across(igafd_ctx* c, RhsDesc rhs, double* b) {
   using R = Run1<P>;
   const Tables T = make_tables(c);
   const Modes md = modes_of(c);
-  const int nq1 = c->dir[0].nel * R::Q, nq2 = c->dir[1].nel * R::Q, n2 = c->n[1];
-  if constexpr (D == 2) {
-    const int runs1 = R::runs(c->n[0]), len1 = R::len(c->n[0]);
-    const int len2 = std::min(n2, std::max(4, cdiv(n2, cdiv(kAsmBlocks, runs1))));
-    const size_t lds = mode_lds(md) + sizeof(double) * R::QS;
-    hipLaunchKernelGGL((k_load2<P>), dim3((unsigned)runs1, 1, (unsigned)cdiv(n2, len2)), dim3(kCol), lds, c->stream, T,
-                       c->geom, md, rhs, b, len1, len2);
-    IGAFD_HIP_CHECK(hipGetLastError());
-  } else {
-    const int n3 = c->n[2], colb = cdiv((long long)nq1 * nq2, kCol);
-    const long long nq12 = (long long)nq1 * nq2, layer = nq12 + (long long)n2 * nq1;
-    const int run = (int)std::min((long long)n3, c->scratch_len / layer);
-    if (run < 1) {
-      set_error("internal: scratch smaller than one plane of moments");
-      return IGAFD_ERR_ARG;
-    }
-    for (int base = 0; base < n3; base += run) {
-      const int end = std::min(n3, base + run);
-      const int len = column_run(end - base, colb);
-      hipLaunchKernelGGL((k_moment3<P, 1>), dim3((unsigned)colb, (unsigned)cdiv(end - base, len)), dim3(kCol),
-                         mode_lds(md), c->stream, T, c->geom, md, rhs, nq1, nq2, (cidx_t*)T.at[2], (ctab_t*)T.qx[2],
-                         (ctab_t*)T.qw[2], (ctab_t*)T.val[2], (ctab_t*)md.d3, base, end,
-                         len, c->scratch);
-      const igafd_status st =
-          moments21<3, P, 1>(c, T, c->scratch, c->scratch + (end - base) * nq12, base, end, b);
-      if (st != IGAFD_OK) return st;
-    }
+  const int nq1 = c->dir[0].nel * R::Q, nq2 = c->dir[1].nel * R::Q, n2 = c->n[1], n3 = c->n[2];
+  const int colb = cdiv((long long)nq1 * nq2, kCol);
+  const long long nq12 = (long long)nq1 * nq2, layer = nq12 + (long long)n2 * nq1;
+  const int run = (int)std::min((long long)n3, c->scratch_len / layer);
+  if (run < 1) {
+    set_error("internal: scratch smaller than one plane of moments");
+    return IGAFD_ERR_ARG;
   }
+  for (int base = 0; base < n3; base += run) {
+    const int end = std::min(n3, base + run);
+    const int len = column_run(end - base, colb);
+    hipLaunchKernelGGL((k_moment3<P, 1>), dim3((unsigned)colb, (unsigned)cdiv(end - base, len)), dim3(kCol),
+                       mode_lds(md), c->stream, T, c->geom, md, rhs, nq1, nq2, (cidx_t*)T.at[2], (ctab_t*)T.qx[2],
+                       (ctab_t*)T.qw[2], (ctab_t*)T.val[2], (ctab_t*)md.d3, base, end, len, c->scratch);
+    const igafd_status st = moments21<P, 1>(c, T, c->scratch, c->scratch + (end - base) * nq12, base, end, b);
+    if (st != IGAFD_OK) return st;
+  }
+  return IGAFD_OK;
+}
+
+template <int D, int P>
+igafd_status launch_elements(igafd_ctx* c, double* acc) {
+  const Tables T = make_tables(c);
+  const int nel[3] = {c->ddir[0].nel, c->ddir[1].nel, D == 3 ? c->ddir[2].nel : 1};
+  const int C3 = (D == 3) ? P + 1 : 1;
+  for (int c3 = 0; c3 < C3; ++c3)
+    for (int c2 = 0; c2 <= P; ++c2)
+      for (int c1 = 0; c1 <= P; ++c1) {
+        const int m1 = c1 < nel[0] ? (nel[0] - c1 + P) / (P + 1) : 0;
+        const int m2 = c2 < nel[1] ? (nel[1] - c2 + P) / (P + 1) : 0;
+        const int m3 = (D == 3) ? (c3 < nel[2] ? (nel[2] - c3 + P) / (P + 1) : 0) : 1;
+        const long long blocks = (long long)m1 * m2 * m3;
+        if (blocks == 0) continue;
+        if (D == 2 && acc)
+          hipLaunchKernelGGL((k_assemble<2, P, 1>), dim3((unsigned)blocks), dim3(kBlock), 0, c->stream, T, c->geom,
+                             c->band + c->halo, c->Ns, c1, c2, c3, m1, m2, c->dflag, acc);
+        else
+          hipLaunchKernelGGL((k_assemble<D, P, 0>), dim3((unsigned)blocks), dim3(kBlock), 0, c->stream, T, c->geom,
+                             c->band + c->halo, c->Ns, c1, c2, c3, m1, m2, c->dflag, nullptr);
+        IGAFD_HIP_CHECK(hipGetLastError());
+      }
+  return IGAFD_OK;
+}
+
+// A's band and, when asked for, the features: across the elements in 3D with
+// features, element by element otherwise (see the head of this file).
+template <int D, int P>
+igafd_status launch_assemble(igafd_ctx* c, bool with_features, AsmWork* work) {
+  if (D == 3 && with_features) return launch_across<P>(c, work);
+  IGAFD_HIP_CHECK(hipMemsetAsync(c->band, 0, sizeof(double) * c->H * c->Ns, c->stream));
+  double* acc = nullptr;
+  igafd_status st;
+  if (with_features) {  // feature sums (8 per dof) assembled with A, kept as FP32 features
+    if ((st = block_alloc((void**)&work->ws, sizeof(double) * 8 * (size_t)c->N)) != IGAFD_OK) return st;
+    acc = work->ws;
+    IGAFD_HIP_CHECK(hipMemsetAsync(acc, 0, sizeof(double) * 8 * (size_t)c->N, c->stream));
+  }
+  if ((st = launch_elements<D, P>(c, acc)) != IGAFD_OK || !acc) return st;
+  hipLaunchKernelGGL(k_features_finish, dim3((unsigned)cdiv(c->N, kBlock)), dim3(kBlock), 0, c->stream, acc, c->feat,
+                     c->N, c->p);
+  IGAFD_HIP_CHECK(hipGetLastError());
+  return IGAFD_OK;
+}
+
+template <int D, int P>
+igafd_status launch_load(igafd_ctx* c, RhsDesc rhs, double* b) {
+  if (D == 3 && c->modes_set) return load_across<P>(c, rhs, b);
+  const Tables T = make_tables(c);
+  IGAFD_HIP_CHECK(hipMemsetAsync(b, 0, sizeof(double) * c->N, c->stream));
+  const int nel[3] = {c->ddir[0].nel, c->ddir[1].nel, D == 3 ? c->ddir[2].nel : 1};
+  const int C3 = (D == 3) ? P + 1 : 1;
+  for (int c3 = 0; c3 < C3; ++c3)
+    for (int c2 = 0; c2 <= P; ++c2)
+      for (int c1 = 0; c1 <= P; ++c1) {
+        const int m1 = c1 < nel[0] ? (nel[0] - c1 + P) / (P + 1) : 0;
+        const int m2 = c2 < nel[1] ? (nel[1] - c2 + P) / (P + 1) : 0;
+        const int m3 = (D == 3) ? (c3 < nel[2] ? (nel[2] - c3 + P) / (P + 1) : 0) : 1;
+        const long long blocks = (long long)m1 * m2 * m3;
+        if (blocks == 0) continue;
+        hipLaunchKernelGGL((k_load<D, P>), dim3((unsigned)blocks), dim3(kBlock), 0, c->stream, T, c->geom, rhs, b,
+                           c1, c2, c3, m1, m2);
+        IGAFD_HIP_CHECK(hipGetLastError());
+      }
   return IGAFD_OK;
 }
 
@@ -1384,7 +1537,9 @@ igafd_status dispatch(int dim, int p, Args... args) {
 
 template <int D, int P>
 struct AssembleOp {
-  static igafd_status run(igafd_ctx* c, bool with_features) { return launch_assemble<D, P>(c, with_features); }
+  static igafd_status run(igafd_ctx* c, bool with_features, AsmWork* w) {
+    return launch_assemble<D, P>(c, with_features, w);
+  }
 };
 template <int D, int P>
 struct FeatureOp {
@@ -1397,44 +1552,45 @@ struct LoadOp {
 
 }  // namespace
 
-// Direction tables of a warped map's modes, kept by the context (assembly and
-// load vectors read them).
+// Direction tables of a warped map's modes, kept by the contexts that assemble
+// across the elements (A, features and load vectors read them).
 igafd_status setup_modes(igafd_ctx* c) {
+  c->modes_set = true;
   const int K = mode_count(c);
   if (K == 0) return IGAFD_OK;
-  const int nq[3] = {c->dir[0].nel * c->dir[0].q, c->dir[1].nel * c->dir[1].q,
-                     c->dim == 3 ? c->dir[2].nel * c->dir[2].q : 1};
+  const int nq[3] = {c->dir[0].nel * c->dir[0].q, c->dir[1].nel * c->dir[1].q, c->dir[2].nel * c->dir[2].q};
   IGAFD_HIP_CHECK(hipMalloc((void**)&c->modes, sizeof(double) * K * (2 * (size_t)nq[0] + 2 * (size_t)nq[1] + 6 * (size_t)nq[2])));
   const Modes m = modes_of(c);
   double *d0 = const_cast<double*>(m.d12[0]), *d1 = const_cast<double*>(m.d12[1]), *d3 = const_cast<double*>(m.d3);
   const dim3 grid((unsigned)cdiv((long long)(nq[0] + nq[1] + nq[2]) * K, 128));
-  if (c->dim == 3)
-    hipLaunchKernelGGL(k_mode_tables<3>, grid, dim3(128), 0, c->stream, c->ddir[0].qx, c->ddir[1].qx, c->ddir[2].qx,
-                       nq[0], nq[1], nq[2], c->geom, K, d0, d1, d3);
-  else
-    hipLaunchKernelGGL(k_mode_tables<2>, grid, dim3(128), 0, c->stream, c->ddir[0].qx, c->ddir[1].qx, c->ddir[1].qx,
-                       nq[0], nq[1], nq[2], c->geom, K, d0, d1, d3);
+  hipLaunchKernelGGL(k_mode_tables, grid, dim3(128), 0, c->stream, c->ddir[0].qx, c->ddir[1].qx, c->ddir[2].qx, nq[0],
+                     nq[1], nq[2], c->geom, K, d0, d1, d3);
   IGAFD_HIP_CHECK(hipGetLastError());
   return IGAFD_OK;
 }
 
 long long load_scratch(const igafd_ctx* c) {  // 3D: the moments of one plane i3
-  if (c->dim != 3) return 0;
+  if (c->dim != 3 || !c->modes_set) return 0;
   const long long nq1 = (long long)c->dir[0].nel * c->dir[0].q, nq2 = (long long)c->dir[1].nel * c->dir[1].q;
   return nq1 * (nq2 + c->n[1]);
 }
 
-igafd_status assemble_band(igafd_ctx* c, bool with_features) {
-  // the zero halo of every plane; the rows in between are all written below
-  const size_t pitch = sizeof(double) * (size_t)c->Ns;
-  const long long tail = c->halo + c->N;
-  IGAFD_HIP_CHECK(hipMemset2DAsync(c->band, pitch, 0, sizeof(double) * (size_t)c->halo, c->H, c->stream));
-  IGAFD_HIP_CHECK(
-      hipMemset2DAsync(c->band + tail, pitch, 0, sizeof(double) * (size_t)(c->Ns - tail), c->H, c->stream));
+AsmWork::~AsmWork() {
+  if (!ws) return;
+  (void)hipStreamSynchronize(stream);
+  block_free(ws);
+}
+
+igafd_status assemble_band(igafd_ctx* c, bool with_features, AsmWork* work) {
   IGAFD_HIP_CHECK(hipMemsetAsync(c->dflag, 0, sizeof(int), c->stream));
-  if (with_features) IGAFD_HIP_CHECK(hipMalloc((void**)&c->feat, sizeof(float) * 8 * (size_t)c->N));
-  const igafd_status st = dispatch<AssembleOp>(c->dim, c->p, c, with_features);
-  if (st != IGAFD_OK) return st;
+  if (with_features) {
+    const igafd_status st = block_alloc((void**)&c->feat, sizeof(float) * 8 * (size_t)c->N);
+    if (st != IGAFD_OK) return st;
+  }
+  return dispatch<AssembleOp>(c->dim, c->p, c, with_features, work);
+}
+
+igafd_status assemble_finish(igafd_ctx* c) {
   int flag = 0;
   IGAFD_HIP_CHECK(hipMemcpyAsync(&flag, c->dflag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   IGAFD_HIP_CHECK(hipStreamSynchronize(c->stream));

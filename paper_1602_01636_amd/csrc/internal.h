@@ -28,6 +28,9 @@ constexpr bool kTile512Default[kMaxDegree + 1] = {false, false, false, true, fal
 constexpr long long kTile512Lds = 128 * 1024;
 
 void set_error(const std::string& msg);
+// large device blocks, recycled between contexts (api.hip)
+igafd_status block_alloc(void** p, size_t bytes);
+void block_free(void* p);
 // block partials (per sum) a context's reductions may write; sizes its buffer
 int partial_capacity(const igafd_ctx* c);
 
@@ -65,6 +68,8 @@ struct Dir1D {
 
 // eig = false: element tables and M, K only (no eigendecomposition)
 igafd_status build_direction(int p, int q, int nknots, const double* knots, Dir1D* out, bool eig = true);
+
+igafd_status eigen_direction(Dir1D* d);  // U and lam of a direction built without them
 
 // Device copies of one direction.
 struct DevDir {
@@ -158,7 +163,8 @@ struct igafd_ctx {
   igafd::SolverState* hstate = nullptr;    // pinned host mirror
   int* dflag = nullptr;                    // device error flag (geometry)
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  double* modes = nullptr;                 // direction tables of a warped map's modes (assembly.hip)
+  bool modes_set = false;                  // A and load vectors are summed across the elements (assembly.hip)
+  double* modes = nullptr;                 // its direction tables of a warped map's modes
   float* feat = nullptr;                   // per-dof features (N x 8) assembled with A, when asked for
   double* hist = nullptr;                  // device residual history of igafd_solve
   int hist_alloc = 0;                      // doubles allocated at hist
@@ -177,9 +183,17 @@ struct igafd_ctx {
 
 namespace igafd {
 // assembly.hip
-igafd_status setup_modes(igafd_ctx* c);
+igafd_status setup_modes(igafd_ctx* c);  // selects the assembly across the elements
 long long load_scratch(const igafd_ctx* c);  // doubles that a load vector needs at least
-igafd_status assemble_band(igafd_ctx* c, bool with_features);
+// A's band (and the features): enqueued on the context's stream with a
+// workspace that is released once the stream has passed it
+struct AsmWork {
+  double* ws;
+  hipStream_t stream;
+  ~AsmWork();
+};
+igafd_status assemble_band(igafd_ctx* c, bool with_features, AsmWork* work);
+igafd_status assemble_finish(igafd_ctx* c);  // waits; IGAFD_ERR_GEOMETRY for det J <= 0
 igafd_status assemble_load(igafd_ctx* c, int rhs_kind, const double* params, int nparams, double* b);
 igafd_status diagonals(igafd_ctx* c, double* dA, double* dP);
 igafd_status features(igafd_ctx* c, float* feat);

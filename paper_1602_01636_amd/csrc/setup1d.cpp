@@ -109,6 +109,77 @@ void parallel_rows(int n, int min_chunk, const F& fn) {
   for (auto& x : th) x.join();
 }
 
+// Inner loops of the eigensolver over rows of doubles, compiled twice: for AVX2
+// where the host has it, and for the baseline.  Every element is computed by
+// the same operations in both (no FMA, no reordered sums), so the results do
+// not depend on the host.
+#define IGAFD_INLINE static inline __attribute__((always_inline))
+
+// y += s x and y -= s x
+IGAFD_INLINE void add_body(double* __restrict__ y, double s, const double* __restrict__ x, int n) {
+  for (int j = 0; j < n; ++j) y[j] += s * x[j];
+}
+IGAFD_INLINE void sub_body(double* __restrict__ y, double s, const double* __restrict__ x, int n) {
+  for (int j = 0; j < n; ++j) y[j] -= s * x[j];
+}
+// y -= a p + b v
+IGAFD_INLINE void rank2_body(double* __restrict__ y, double a, const double* __restrict__ p, double b,
+                             const double* __restrict__ v, int n) {
+  for (int j = 0; j < n; ++j) y[j] -= a * p[j] + b * v[j];
+}
+// rotations q = 0..nrot-1 on the rows rk[q], rk[q] + 1 of T (rows of kRotRows values)
+constexpr int kRotRows = 32;
+IGAFD_INLINE void rotate_body(double* T, const int* rk, const double* rc, const double* rs, size_t nrot) {
+  for (size_t q = 0; q < nrot; ++q) {
+    double* __restrict__ a = T + (size_t)rk[q] * kRotRows;
+    double* __restrict__ b = a + kRotRows;
+    const double c = rc[q], s = rs[q];
+    for (int j = 0; j < kRotRows; ++j) {
+      const double va = a[j], vb = b[j];
+      a[j] = c * va + s * vb;
+      b[j] = -s * va + c * vb;
+    }
+  }
+}
+
+void add_base(double* y, double s, const double* x, int n) { add_body(y, s, x, n); }
+void sub_base(double* y, double s, const double* x, int n) { sub_body(y, s, x, n); }
+void rank2_base(double* y, double a, const double* p, double b, const double* v, int n) { rank2_body(y, a, p, b, v, n); }
+void rotate_base(double* T, const int* rk, const double* rc, const double* rs, size_t n) { rotate_body(T, rk, rc, rs, n); }
+#ifndef __HIP_DEVICE_COMPILE__  // host code only; the device pass of hipcc knows no x86 features
+#define IGAFD_AVX2 __attribute__((target("avx2")))
+IGAFD_AVX2 void add_avx2(double* y, double s, const double* x, int n) { add_body(y, s, x, n); }
+IGAFD_AVX2 void sub_avx2(double* y, double s, const double* x, int n) { sub_body(y, s, x, n); }
+IGAFD_AVX2 void rank2_avx2(double* y, double a, const double* p, double b, const double* v, int n) {
+  rank2_body(y, a, p, b, v, n);
+}
+IGAFD_AVX2 void rotate_avx2(double* T, const int* rk, const double* rc, const double* rs, size_t n) {
+  rotate_body(T, rk, rc, rs, n);
+}
+#endif
+
+struct RowOps {
+  void (*add)(double*, double, const double*, int) = add_base;
+  void (*sub)(double*, double, const double*, int) = sub_base;
+  void (*rank2)(double*, double, const double*, double, const double*, int) = rank2_base;
+  void (*rotate)(double*, const int*, const double*, const double*, size_t) = rotate_base;
+  RowOps() {
+#ifndef __HIP_DEVICE_COMPILE__
+    __builtin_cpu_init();
+    if (__builtin_cpu_supports("avx2")) {
+      add = add_avx2;
+      sub = sub_avx2;
+      rank2 = rank2_avx2;
+      rotate = rotate_avx2;
+    }
+#endif
+  }
+};
+const RowOps& ops() {
+  static const RowOps o;
+  return o;
+}
+
 // Largest |i - j| with A_ij != 0 (A n x n, row-major).
 int bandwidth(const std::vector<double>& A, int n) {
   int bw = 0;
@@ -148,9 +219,7 @@ void forward_rows(const std::vector<double>& L, int n, int bw, std::vector<doubl
   for (int i = 0; i < n; ++i) {
     double* xi = &X[(size_t)i * n];
     for (int k = std::max(0, i - bw); k < i; ++k) {
-      const double l = L[(size_t)i * n + k];
-      const double* xk = &X[(size_t)k * n];
-      for (int j = 0; j < n; ++j) xi[j] -= l * xk[j];
+      ops().sub(xi, L[(size_t)i * n + k], &X[(size_t)k * n], n);
     }
     const double d = L[(size_t)i * n + i];
     for (int j = 0; j < n; ++j) xi[j] /= d;
@@ -164,20 +233,24 @@ void forward_rows(const std::vector<double>& L, int n, int bw, std::vector<doubl
 // The QR steps run on the tridiagonal alone; their plane rotations are
 // recorded and applied to V afterwards, a block of rows at a time.
 void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std::vector<double>& V) {
-  V.assign((size_t)n * n, 0.0);
-  for (int i = 0; i < n; ++i) V[(size_t)i * n + i] = 1.0;
-  std::vector<double> v(n), pv(n);
-  constexpr int kMinRows = 128;
-  // 1. S = Q T Q^T: reflector k zeroes column k below the subdiagonal
+  std::vector<double> Vt((size_t)n * n, 0.0);  // V transposed
+  for (int i = 0; i < n; ++i) Vt[(size_t)i * n + i] = 1.0;
+  std::vector<double> v(n), pv(n), tv(n);
+  constexpr int kMinCols = 256;  // columns per thread at least: a thread start costs about 20 us
+  const RowOps& op = ops();
+  // 1. S = Q T Q^T: reflector k zeroes column k below the subdiagonal.  The
+  // matrix-vector products run over rows (S is symmetric to the last bit: its
+  // update is), each element summed in ascending order.
   for (int k = 0; k + 2 < n; ++k) {
     const int m = n - k - 1;  // length of x = S[k+1:, k]
+    const double* x = &S[(size_t)k * n + k + 1];
     double nx = 0.0;
-    for (int i = 0; i < m; ++i) nx += S[(size_t)(k + 1 + i) * n + k] * S[(size_t)(k + 1 + i) * n + k];
+    for (int i = 0; i < m; ++i) nx += x[i] * x[i];
     nx = std::sqrt(nx);
     if (nx == 0.0) continue;
-    const double x0 = S[(size_t)(k + 1) * n + k];
+    const double x0 = x[0];
     const double alpha = x0 >= 0 ? -nx : nx;
-    for (int i = 0; i < m; ++i) v[i] = S[(size_t)(k + 1 + i) * n + k];
+    for (int i = 0; i < m; ++i) v[i] = x[i];
     v[0] -= alpha;
     double nv = 0.0;
     for (int i = 0; i < m; ++i) nv += v[i] * v[i];
@@ -185,35 +258,25 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
     if (nv == 0.0) continue;
     for (int i = 0; i < m; ++i) v[i] /= nv;
     // trailing block B <- H B H = B - 2 v w^T - 2 w v^T, w = B v - (v^T B v) v
-    parallel_rows(m, kMinRows, [&](int lo, int hi) {
-      for (int i = lo; i < hi; ++i) {
-        const double* row = &S[(size_t)(k + 1 + i) * n + k + 1];
-        double t = 0.0;
-        for (int j = 0; j < m; ++j) t += row[j] * v[j];
-        pv[i] = t;
-      }
+    parallel_rows(m, kMinCols, [&](int lo, int hi) {
+      for (int i = lo; i < hi; ++i) pv[i] = 0.0;
+      for (int j = 0; j < m; ++j) op.add(&pv[lo], v[j], &S[(size_t)(k + 1 + j) * n + k + 1 + lo], hi - lo);
     });
     double cvp = 0.0;
     for (int i = 0; i < m; ++i) cvp += v[i] * pv[i];
     for (int i = 0; i < m; ++i) pv[i] -= cvp * v[i];
-    parallel_rows(m, kMinRows, [&](int lo, int hi) {
-      for (int i = lo; i < hi; ++i) {
-        double* row = &S[(size_t)(k + 1 + i) * n + k + 1];
-        const double vi = 2.0 * v[i], pi = 2.0 * pv[i];
-        for (int j = 0; j < m; ++j) row[j] -= vi * pv[j] + pi * v[j];
-      }
+    parallel_rows(m, kMinCols, [&](int lo, int hi) {
+      for (int i = lo; i < hi; ++i)
+        op.rank2(&S[(size_t)(k + 1 + i) * n + k + 1], 2.0 * v[i], pv.data(), 2.0 * pv[i], v.data(), m);
     });
     S[(size_t)(k + 1) * n + k] = S[(size_t)k * n + k + 1] = alpha;
     for (int i = 1; i < m; ++i) S[(size_t)(k + 1 + i) * n + k] = S[(size_t)k * n + k + 1 + i] = 0.0;
-    // V <- V H on columns k+1..n-1
-    parallel_rows(n, kMinRows, [&](int lo, int hi) {
-      for (int r = lo; r < hi; ++r) {
-        double* row = &V[(size_t)r * n + k + 1];
-        double t = 0.0;
-        for (int j = 0; j < m; ++j) t += row[j] * v[j];
-        t *= 2.0;
-        for (int j = 0; j < m; ++j) row[j] -= t * v[j];
-      }
+    // V <- V H on columns k+1..n-1 (rows of V^T)
+    parallel_rows(n, kMinCols, [&](int lo, int hi) {
+      for (int r = lo; r < hi; ++r) tv[r] = 0.0;
+      for (int j = 0; j < m; ++j) op.add(&tv[lo], v[j], &Vt[(size_t)(k + 1 + j) * n + lo], hi - lo);
+      for (int r = lo; r < hi; ++r) tv[r] *= 2.0;
+      for (int j = 0; j < m; ++j) op.sub(&Vt[(size_t)(k + 1 + j) * n + lo], v[j], &tv[lo], hi - lo);
     });
   }
   std::vector<double> d(n), e(n, 0.0);
@@ -260,26 +323,18 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
       rs.push_back(s);
     }
   }
-  // 3. V <- V G_1 G_2 ...: blocks of B rows, stored transposed so that one
-  // rotation updates two contiguous runs of B values
-  constexpr int B = 32;
+  // 3. V <- V G_1 G_2 ...: blocks of rows of V, stored transposed so that one
+  // rotation updates two contiguous runs
+  V.assign((size_t)n * n, 0.0);
+  constexpr int B = kRotRows;
   const size_t nrot = rk.size();
-  parallel_rows((n + B - 1) / B, 1, [&](int blo, int bhi) {
+  parallel_rows((n + B - 1) / B, n < 256 ? n : 1, [&](int blo, int bhi) {
     std::vector<double> T((size_t)n * B);
     for (int blk = blo; blk < bhi; ++blk) {
       const int r0 = blk * B, nb = std::min(B, n - r0);
-      for (int j = 0; j < nb; ++j)
-        for (int k = 0; k < n; ++k) T[(size_t)k * B + j] = V[(size_t)(r0 + j) * n + k];
-      for (size_t q = 0; q < nrot; ++q) {
-        double* a = &T[(size_t)rk[q] * B];
-        double* b = a + B;
-        const double c = rc[q], s = rs[q];
-        for (int j = 0; j < B; ++j) {
-          const double va = a[j], vb = b[j];
-          a[j] = c * va + s * vb;
-          b[j] = -s * va + c * vb;
-        }
-      }
+      for (int k = 0; k < n; ++k)
+        for (int j = 0; j < nb; ++j) T[(size_t)k * B + j] = Vt[(size_t)k * n + r0 + j];
+      op.rotate(T.data(), rk.data(), rc.data(), rs.data(), nrot);
       for (int j = 0; j < nb; ++j)
         for (int k = 0; k < n; ++k) V[(size_t)(r0 + j) * n + k] = T[(size_t)k * B + j];
     }
@@ -391,7 +446,12 @@ igafd_status build_direction(int p, int q, int nknots, const double* knots, Dir1
   }
   d.U.clear();
   d.lam.clear();
-  if (!eig) return IGAFD_OK;
+  return eig ? eigen_direction(out) : IGAFD_OK;
+}
+
+igafd_status eigen_direction(Dir1D* out) {
+  Dir1D& d = *out;
+  const int n = d.n;
   // generalised eigendecomposition K U = M U D, U^T M U = I
   const int bw = bandwidth(d.M, n);
   std::vector<double> L = d.M;
@@ -418,9 +478,7 @@ igafd_status build_direction(int p, int q, int nknots, const double* knots, Dir1
   for (int i = n - 1; i >= 0; --i) {
     double* ui = &d.U[(size_t)i * n];
     for (int k = i + 1; k <= std::min(n - 1, i + bw); ++k) {
-      const double l = L[(size_t)k * n + i];
-      const double* uk = &d.U[(size_t)k * n];
-      for (int j = 0; j < n; ++j) ui[j] -= l * uk[j];
+      ops().sub(ui, L[(size_t)k * n + i], &d.U[(size_t)k * n], n);
     }
     const double dd = L[(size_t)i * n + i];
     for (int j = 0; j < n; ++j) ui[j] /= dd;

@@ -1,4 +1,4 @@
-"""Assembly kernels (direction-by-direction sum factorisation) against the
+"""Assembly kernels (across the elements and element by element) against the
 oracle's element loops, at the sizes where the walks and the runs can go wrong:
 runs of direction-1 functions that end on and next to a block's limit, several
 runs of planes, repeated knots up to multiplicity p (an element shift of more
@@ -53,13 +53,15 @@ def cases():
 CASES = cases()
 
 
+@pytest.mark.parametrize("features", [True, False], ids=["across", "elements"])
 @pytest.mark.parametrize("name,prob", CASES, ids=[c[0] for c in CASES])
-def test_assembly_matches_oracle(name, prob, rng):
+def test_assembly_matches_oracle(name, prob, features, rng):
+    """features=True: 3D contexts assemble across the elements, else element by element."""
     import torch
 
     import paper_1602_01636_amd as api
     A = assembly.assemble_matrix(prob)
-    with api.igafd_setup(prob, features=True) as ctx:
+    with api.igafd_setup(prob, features=features) as ctx:
         N = ctx.N
         assert N == A.shape[0]
         x = rng.standard_normal(N)
@@ -76,8 +78,3 @@ def test_assembly_matches_oracle(name, prob, rng):
         feat = torch.full((8 * N,), float("nan"), dtype=torch.float32, device="cuda")
         api.igafd_features(ctx, feat)
         np.testing.assert_allclose(to_host(feat).reshape(-1, 8), omlp.features(prob), rtol=2e-6, atol=2e-7)
-    # a preconditioner-only context takes the load vector's scratch from fewer vectors
-    with api.igafd_setup_precond(prob) as pc:
-        b2 = to_dev(np.full(N, np.nan))
-        api.igafd_load_vector(pc, synth.RHS_BUBBLE, b2)
-        assert np.array_equal(to_host(b2), to_host(b))
