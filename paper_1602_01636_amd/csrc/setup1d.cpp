@@ -7,8 +7,10 @@
 // symmetric eigendecomposition of L^-1 K L^-T, U = L^-T Ut).  The symmetric
 // eigensolver is Householder tridiagonalisation plus implicit shifted QR.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -235,49 +237,92 @@ void forward_rows(const std::vector<double>& L, int n, int bw, std::vector<doubl
 void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std::vector<double>& V) {
   std::vector<double> Vt((size_t)n * n, 0.0);  // V transposed
   for (int i = 0; i < n; ++i) Vt[(size_t)i * n + i] = 1.0;
-  std::vector<double> v(n), pv(n), tv(n);
-  constexpr int kMinCols = 256;  // columns per thread at least: a thread start costs about 20 us
+  std::vector<double> pv(n);
   const RowOps& op = ops();
   // 1. S = Q T Q^T: reflector k zeroes column k below the subdiagonal.  The
   // matrix-vector products run over rows (S is symmetric to the last bit: its
-  // update is), each element summed in ascending order.
-  for (int k = 0; k + 2 < n; ++k) {
-    const int m = n - k - 1;  // length of x = S[k+1:, k]
-    const double* x = &S[(size_t)k * n + k + 1];
-    double nx = 0.0;
-    for (int i = 0; i < m; ++i) nx += x[i] * x[i];
-    nx = std::sqrt(nx);
-    if (nx == 0.0) continue;
-    const double x0 = x[0];
-    const double alpha = x0 >= 0 ? -nx : nx;
-    for (int i = 0; i < m; ++i) v[i] = x[i];
-    v[0] -= alpha;
-    double nv = 0.0;
-    for (int i = 0; i < m; ++i) nv += v[i] * v[i];
-    nv = std::sqrt(nv);
-    if (nv == 0.0) continue;
-    for (int i = 0; i < m; ++i) v[i] /= nv;
-    // trailing block B <- H B H = B - 2 v w^T - 2 w v^T, w = B v - (v^T B v) v
-    parallel_rows(m, kMinCols, [&](int lo, int hi) {
+  // update is), each element summed in ascending order.  From kTeamMin on, a team
+  // of threads runs the whole loop, each on a share of the columns (rows in the
+  // update of S), with the scalars and v computed by every thread: below, the two
+  // barriers per reflector cost more than they save (n = 515: 35 ms alone; a
+  // thread started per product and reflector: 90).
+  constexpr int kTeamMin = 600, kTeamCols = 96;
+  auto reflect = [&](int t, int T, auto&& barrier) {
+    std::vector<double> v(n), w(n), tv(n);
+    auto share = [&](int m, int* lo, int* hi) {
+      *lo = (int)((long long)m * t / T);
+      *hi = (int)((long long)m * (t + 1) / T);
+    };
+    int lo, hi;
+    for (int k = 0; k + 2 < n; ++k) {
+      const int m = n - k - 1;  // length of x = S[k+1:, k]
+      const double* x = &S[(size_t)k * n + k + 1];
+      double nx = 0.0;
+      for (int i = 0; i < m; ++i) nx += x[i] * x[i];
+      nx = std::sqrt(nx);
+      if (nx == 0.0) continue;
+      const double x0 = x[0];
+      const double alpha = x0 >= 0 ? -nx : nx;
+      for (int i = 0; i < m; ++i) v[i] = x[i];
+      v[0] -= alpha;
+      double nv = 0.0;
+      for (int i = 0; i < m; ++i) nv += v[i] * v[i];
+      nv = std::sqrt(nv);
+      if (nv == 0.0) continue;
+      for (int i = 0; i < m; ++i) v[i] /= nv;
+      // trailing block B <- H B H = B - 2 v w^T - 2 w v^T, w = B v - (v^T B v) v
+      share(m, &lo, &hi);
       for (int i = lo; i < hi; ++i) pv[i] = 0.0;
-      for (int j = 0; j < m; ++j) op.add(&pv[lo], v[j], &S[(size_t)(k + 1 + j) * n + k + 1 + lo], hi - lo);
-    });
-    double cvp = 0.0;
-    for (int i = 0; i < m; ++i) cvp += v[i] * pv[i];
-    for (int i = 0; i < m; ++i) pv[i] -= cvp * v[i];
-    parallel_rows(m, kMinCols, [&](int lo, int hi) {
+      for (int j = 0; j < m && lo < hi; ++j) op.add(&pv[lo], v[j], &S[(size_t)(k + 1 + j) * n + k + 1 + lo], hi - lo);
+      barrier();
+      double cvp = 0.0;
+      for (int i = 0; i < m; ++i) cvp += v[i] * pv[i];
+      for (int i = 0; i < m; ++i) w[i] = pv[i] - cvp * v[i];
       for (int i = lo; i < hi; ++i)
-        op.rank2(&S[(size_t)(k + 1 + i) * n + k + 1], 2.0 * v[i], pv.data(), 2.0 * pv[i], v.data(), m);
-    });
-    S[(size_t)(k + 1) * n + k] = S[(size_t)k * n + k + 1] = alpha;
-    for (int i = 1; i < m; ++i) S[(size_t)(k + 1 + i) * n + k] = S[(size_t)k * n + k + 1 + i] = 0.0;
-    // V <- V H on columns k+1..n-1 (rows of V^T)
-    parallel_rows(n, kMinCols, [&](int lo, int hi) {
+        op.rank2(&S[(size_t)(k + 1 + i) * n + k + 1], 2.0 * v[i], w.data(), 2.0 * w[i], v.data(), m);
+      if (t == 0) {  // column and row k of S are read by nobody before the barrier
+        S[(size_t)(k + 1) * n + k] = alpha;
+        for (int i = 1; i < m; ++i) S[(size_t)(k + 1 + i) * n + k] = 0.0;
+      }
+      // V <- V H on columns k+1..n-1 (rows of V^T)
+      share(n, &lo, &hi);
       for (int r = lo; r < hi; ++r) tv[r] = 0.0;
-      for (int j = 0; j < m; ++j) op.add(&tv[lo], v[j], &Vt[(size_t)(k + 1 + j) * n + lo], hi - lo);
+      for (int j = 0; j < m && lo < hi; ++j) op.add(&tv[lo], v[j], &Vt[(size_t)(k + 1 + j) * n + lo], hi - lo);
       for (int r = lo; r < hi; ++r) tv[r] *= 2.0;
-      for (int j = 0; j < m; ++j) op.sub(&Vt[(size_t)(k + 1 + j) * n + lo], v[j], &tv[lo], hi - lo);
-    });
+      for (int j = 0; j < m && lo < hi; ++j) op.sub(&Vt[(size_t)(k + 1 + j) * n + lo], v[j], &tv[lo], hi - lo);
+      barrier();
+    }
+  };
+  const int team = n < kTeamMin ? 1 : std::max(1, std::min(std::min(16, n / kTeamCols),
+                                                           (int)std::thread::hardware_concurrency()));
+  if (team == 1) {
+    reflect(0, 1, []() {});
+  } else {
+    std::atomic<int> arrived{0}, phase{0}, size{0};
+    auto barrier = [&]() {
+      const int ph = phase.load(std::memory_order_acquire);
+      if (arrived.fetch_add(1, std::memory_order_acq_rel) + 1 == size.load(std::memory_order_relaxed)) {
+        arrived.store(0, std::memory_order_relaxed);
+        phase.store(ph + 1, std::memory_order_release);
+      } else {
+        for (int spin = 0; phase.load(std::memory_order_acquire) == ph; ++spin)
+          if (spin > 2000) std::this_thread::yield();
+      }
+    };
+    std::vector<std::thread> th;
+    std::atomic<bool> go{false};
+    try {
+      for (int t = 1; t < team; ++t)
+        th.emplace_back([&, t]() {
+          while (!go.load(std::memory_order_acquire)) std::this_thread::yield();
+          reflect(t, size.load(std::memory_order_relaxed), barrier);
+        });
+    } catch (const std::system_error&) {  // fewer threads than asked for
+    }
+    size.store((int)th.size() + 1, std::memory_order_relaxed);
+    go.store(true, std::memory_order_release);
+    reflect(0, (int)th.size() + 1, barrier);
+    for (auto& x : th) x.join();
   }
   std::vector<double> d(n), e(n, 0.0);
   for (int i = 0; i < n; ++i) d[i] = S[(size_t)i * n + i];
