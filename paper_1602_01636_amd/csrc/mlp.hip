@@ -15,8 +15,8 @@
 // the forward pass or in the back-propagation of the input gradient.  Weight
 // gradients contract over samples: each wave transposes its 16-sample tiles
 // through LDS, accumulates them in MFMA registers over all its sample groups,
-// and writes one partial per wave; a fixed-order reduction finishes them
-// (deterministic, no atomics).
+// and the waves of a block add to one partial in LDS; a fixed-order reduction
+// over the blocks finishes them, with the Adam step (deterministic, no atomics).
 #include <cmath>
 #include <cstring>
 #include <random>
@@ -29,7 +29,7 @@ struct igafd_mlp {
   float* adam_m = nullptr;
   float* adam_v = nullptr;
   float* grad = nullptr;
-  float* partial = nullptr;  // per-wave partial gradients (+ loss)
+  float* partial = nullptr;  // per-block partial gradients (+ loss)
   float* norm = nullptr;     // mean[8], 1/std[8]
   short* w1b = nullptr;      // BF16 W1 as [64][16] (inputs zero padded)
   short* w2b = nullptr;      // BF16 W2 as [64][64]
@@ -45,7 +45,9 @@ constexpr int NIN = 8, NH = 64;
 constexpr int OW1 = 0, OB1 = OW1 + NH * NIN, OW2 = OB1 + NH, OB2 = OW2 + NH * NH, OW3 = OB2 + NH, OB3 = OW3 + NH;
 constexpr int NPARAM = OB3 + 1;  // 4801
 constexpr int MAXWAVES = 1024;
-constexpr int WPB = kBlock / 64;  // waves per block
+// waves per block: two when training, so that the 512 waves of an 8192-sample
+// batch reach every CU and a block's sums take one step in LDS
+constexpr int wpb(int train) { return train ? 2 : kBlock / 64; }
 
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef short s4_t __attribute__((ext_vector_type(4)));
@@ -70,13 +72,14 @@ __device__ inline float sum_over_samples(float v) {  // over the 16 lanes of one
 }
 
 // TRAIN = 0: t (and S = exp t) for n samples.  TRAIN = 1: gradients of
-// L = (1/n) sum (t - target)^2 into per-wave partials.
+// L = (1/n) sum (t - target)^2 into per-block partials.
 template <int TRAIN>
-__global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta, const short* __restrict__ w1b,
+__global__ __launch_bounds__(64 * wpb(TRAIN)) void k_mlp(const float* __restrict__ theta, const short* __restrict__ w1b,
                                                 const short* __restrict__ w2b, const short* __restrict__ w2tb,
                                                 const float* __restrict__ norm, const float* __restrict__ feat,
                                                 const float* __restrict__ target, long long n, float* __restrict__ t_out,
                                                 double* __restrict__ S_out, float* __restrict__ partial) {
+  constexpr int WPB = wpb(TRAIN);
   __shared__ short s_dz2[WPB][NH][16];
   __shared__ short s_h1[WPB][NH][16];
   __shared__ short s_dz1[WPB][NH][16];
@@ -97,6 +100,26 @@ __global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta,
     }
   }
 
+  // the lane's weights and biases, all loads issued before the first is waited
+  // for (they were written by the previous step's kernel: every one misses L2)
+  s4_t a1[4], a2[4][4], a3[4][4];
+  float c1[4][4], c2[4][4], c3[4][4];
+  const float c4 = theta[OB3];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    a1[m] = load4(w1b + (16 * m + col) * 16 + 4 * grp);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      a2[m][k] = load4(w2b + (16 * m + col) * NH + 16 * k + 4 * grp);
+      if (TRAIN) a3[m][k] = load4(w2tb + (16 * m + col) * NH + 16 * k + 4 * grp);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      c1[m][r] = theta[OB1 + 16 * m + 4 * grp + r];
+      c2[m][r] = theta[OB2 + 16 * m + 4 * grp + r];
+      c3[m][r] = theta[OW3 + 16 * m + 4 * grp + r];
+    }
+  }
   for (long long g = gwave; g < ngroups; g += nwaves) {
     const long long s = g * 16 + col;
     const bool live = s < n;
@@ -111,9 +134,9 @@ __global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta,
     float h1[4][4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-      f4_t d = mma(load4(w1b + (16 * m + col) * 16 + 4 * grp), bF, f4_t{0, 0, 0, 0});
+      f4_t d = mma(a1[m], bF, f4_t{0, 0, 0, 0});
 #pragma unroll
-      for (int r = 0; r < 4; ++r) h1[m][r] = tanhf(d[r] + theta[OB1 + 16 * m + 4 * grp + r]);
+      for (int r = 0; r < 4; ++r) h1[m][r] = tanhf(d[r] + c1[m][r]);
     }
     s4_t bH1[4];
 #pragma unroll
@@ -124,19 +147,19 @@ __global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta,
     for (int o = 0; o < 4; ++o) {
       f4_t d = {0, 0, 0, 0};
 #pragma unroll
-      for (int m = 0; m < 4; ++m) d = mma(load4(w2b + (16 * o + col) * NH + 16 * m + 4 * grp), bH1[m], d);
+      for (int m = 0; m < 4; ++m) d = mma(a2[o][m], bH1[m], d);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) h2[o][r] = tanhf(d[r] + theta[OB2 + 16 * o + 4 * grp + r]);
+      for (int r = 0; r < 4; ++r) h2[o][r] = tanhf(d[r] + c2[o][r]);
     }
     // layer 3: t = w3 . h2 + b3 (lane-local partial, then over the 4 lane groups)
     float part = 0.f;
 #pragma unroll
     for (int o = 0; o < 4; ++o)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) part += theta[OW3 + 16 * o + 4 * grp + r] * h2[o][r];
+      for (int r = 0; r < 4; ++r) part += c3[o][r] * h2[o][r];
     part += __shfl_xor(part, 16, 64);
     part += __shfl_xor(part, 32, 64);
-    const float t = part + theta[OB3];
+    const float t = part + c4;
     if (!TRAIN) {
       if (grp == 0 && live) {
         if (t_out) t_out[s] = t;
@@ -156,7 +179,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta,
     for (int o = 0; o < 4; ++o)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        dz2[o][r] = dt * theta[OW3 + 16 * o + 4 * grp + r] * (1.f - h2[o][r] * h2[o][r]);
+        dz2[o][r] = dt * c3[o][r] * (1.f - h2[o][r] * h2[o][r]);
         gw3[o][r] += dt * h2[o][r];
         gb2[o][r] += dz2[o][r];
       }
@@ -170,7 +193,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta,
     for (int m = 0; m < 4; ++m) {
       f4_t d = {0, 0, 0, 0};
 #pragma unroll
-      for (int o = 0; o < 4; ++o) d = mma(load4(w2tb + (16 * m + col) * NH + 16 * o + 4 * grp), bDz2[o], d);
+      for (int o = 0; o < 4; ++o) d = mma(a3[m][o], bDz2[o], d);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         dz1[m][r] = d[r] * (1.f - h1[m][r] * h1[m][r]);
@@ -204,7 +227,10 @@ __global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta,
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
   if (!TRAIN) return;
-  float* out = partial + (long long)gwave * (NPARAM + 1);
+  // the block's sums: an LDS image per wave, added on the way out, so that a
+  // block and not a wave writes the 4802 values that k_mlp_step reads again
+  __shared__ float s_sum[TRAIN ? WPB : 1][TRAIN ? NPARAM + 1 : 1];
+  float* im = s_sum[wv];
   // result lane layout: row 4 grp + r, column col of each 16 x 16 tile
 #pragma unroll
   for (int a = 0; a < 4; ++a)
@@ -212,8 +238,8 @@ __global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta,
     for (int r = 0; r < 4; ++r) {
       const int o = 16 * a + 4 * grp + r;
 #pragma unroll
-      for (int b = 0; b < 4; ++b) out[OW2 + o * NH + 16 * b + col] = gW2[a][b][r];
-      if (col < NIN) out[OW1 + o * NIN + col] = gW1[a][r];
+      for (int b = 0; b < 4; ++b) im[OW2 + o * NH + 16 * b + col] = gW2[a][b][r];
+      if (col < NIN) im[OW1 + o * NIN + col] = gW1[a][r];
     }
   // per-neuron sums over the 16 sample lanes of each lane group
 #pragma unroll
@@ -225,55 +251,86 @@ __global__ __launch_bounds__(kBlock) void k_mlp(const float* __restrict__ theta,
       const float v3 = sum_over_samples(gw3[m][r]);
       if (col == 0) {
         const int nrn = 16 * m + 4 * grp + r;
-        out[OB1 + nrn] = v1;
-        out[OB2 + nrn] = v2;
-        out[OW3 + nrn] = v3;
+        im[OB1 + nrn] = v1;
+        im[OB2 + nrn] = v2;
+        im[OW3 + nrn] = v3;
       }
     }
   const float tb3 = sum_over_samples(gb3);
   const float tl = sum_over_samples(loss);
   if (lane == 0) {
-    out[OB3] = tb3;
-    out[NPARAM] = tl;
+    im[OB3] = tb3;
+    im[NPARAM] = tl;
+  }
+  __syncthreads();
+  float* out = partial + (long long)blockIdx.x * (NPARAM + 1);
+  for (int k = threadIdx.x; k <= NPARAM; k += 64 * WPB) out[k] = s_sum[0][k] + s_sum[TRAIN ? WPB - 1 : 0][k];
+}
+
+// The parameter's BF16 copies (W1 padded to 16 inputs, W2 and W2^T).
+__device__ inline void refresh_param(int k, float v, short* __restrict__ w1b, short* __restrict__ w2b,
+                                     short* __restrict__ w2tb) {
+  if (k < OB1) {
+    w1b[(k / NIN) * 16 + k % NIN] = bf16_of(v);
+  } else if (k >= OW2 && k < OB2) {
+    const int q = k - OW2, o = q / NH, i = q % NH;
+    w2b[q] = bf16_of(v);
+    w2tb[i * NH + o] = bf16_of(v);
   }
 }
 
-// grad[k] = sum over waves of partial[w][k] (fixed order); loss = sum / n.
-__global__ void k_mlp_reduce(const float* __restrict__ partial, int nw, float* __restrict__ grad,
-                             float* __restrict__ loss, long long n) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > NPARAM) return;
-  float s = 0.f;
-  for (int w = 0; w < nw; ++w) s += partial[(long long)w * (NPARAM + 1) + k];
-  if (k < NPARAM)
-    grad[k] = s;
-  else
-    *loss = s / (float)n;
+// grad[k] = sum of the blocks' partials (fixed order); loss = sum / n.  With
+// lr > 0 also the Adam step and the BF16 copies of the new parameter.  A block
+// owns kStepCols parameters and its kStepRows rows of threads each a share of
+// the partials, eight loads in flight, so the 256 partials of an 8192-sample
+// batch take two trips to memory and not 256 in sequence: 4.0 us, where
+// reduction, Adam and copies in three launches, one thread per parameter over
+// the partials of 512 waves, took 113.6 + 4.7 + 4.6 us.  The step is bound by
+// the dependent chain of k_mlp's one sample group per wave (16.7 us; 20.1 with
+// the weights loaded where they are used and four waves on half of the CUs).
+constexpr int kStepCols = 32, kStepRows = 16;
+__global__ __launch_bounds__(kStepCols * kStepRows) void k_mlp_step(const float* __restrict__ partial, int nb,
+                                                                    float* __restrict__ grad,
+                                                                    float* __restrict__ loss, long long n, float lr,
+                                                                    float c1, float c2, float* __restrict__ theta,
+                                                                    float* __restrict__ m, float* __restrict__ v,
+                                                                    short* __restrict__ w1b, short* __restrict__ w2b,
+                                                                    short* __restrict__ w2tb) {
+  __shared__ float s[kStepRows][kStepCols + 1];
+  const int c = threadIdx.x % kStepCols, row = threadIdx.x / kStepCols;
+  const int k = blockIdx.x * kStepCols + c;
+  float a = 0.f;
+  if (k <= NPARAM) {
+#pragma unroll 8
+    for (int w = row; w < nb; w += kStepRows) a += partial[(long long)w * (NPARAM + 1) + k];
+  }
+  s[row][c] = a;
+  __syncthreads();
+  if (row != 0 || k > NPARAM) return;
+  float g = 0.f;
+#pragma unroll
+  for (int r = 0; r < kStepRows; ++r) g += s[r][c];
+  if (k == NPARAM) {
+    *loss = g / (float)n;
+    return;
+  }
+  grad[k] = g;
+  if (!(lr > 0.f)) return;
+  const float b1 = 0.9f, b2 = 0.999f;
+  const float mk = b1 * m[k] + (1.f - b1) * g, vk = b2 * v[k] + (1.f - b2) * g * g;
+  m[k] = mk;
+  v[k] = vk;
+  const float t = theta[k] - lr * (mk / c1) / (sqrtf(vk / c2) + 1e-8f);
+  theta[k] = t;
+  refresh_param(k, t, w1b, w2b, w2tb);
 }
 
-// BF16 copies of the weight matrices (W1 padded to 16 inputs, W2 and W2^T).
+// BF16 copies of all weight matrices; the padding inputs of W1 zero
 __global__ void k_mlp_refresh(const float* __restrict__ theta, short* __restrict__ w1b, short* __restrict__ w2b,
                               short* __restrict__ w2tb) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < NH * 16) {
-    const int o = k / 16, i = k % 16;
-    w1b[k] = bf16_of(i < NIN ? theta[OW1 + o * NIN + i] : 0.f);
-  }
-  if (k < NH * NH) {
-    const int o = k / NH, i = k % NH;
-    w2b[k] = bf16_of(theta[OW2 + k]);
-    w2tb[i * NH + o] = bf16_of(theta[OW2 + k]);
-  }
-}
-
-__global__ void k_mlp_adam(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
-                           const float* __restrict__ g, float lr, float c1, float c2) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= NPARAM) return;
-  const float b1 = 0.9f, b2 = 0.999f;
-  m[k] = b1 * m[k] + (1.f - b1) * g[k];
-  v[k] = b2 * v[k] + (1.f - b2) * g[k] * g[k];
-  theta[k] -= lr * (m[k] / c1) / (sqrtf(v[k] / c2) + 1e-8f);
+  if (k < NPARAM) refresh_param(k, theta[k], w1b, w2b, w2tb);
+  if (k < NH * (16 - NIN)) w1b[(k / (16 - NIN)) * 16 + NIN + k % (16 - NIN)] = 0;
 }
 
 // mean and 1/std of each of the 8 inputs (one block per input, fixed order)
@@ -302,27 +359,28 @@ __global__ void k_mlp_norm(const float* __restrict__ feat, long long n, float* _
   }
 }
 
-int waves_for(long long n) {
-  const long long groups = (n + 15) / 16;
-  long long w = groups < MAXWAVES ? groups : MAXWAVES;
-  w = (w + WPB - 1) / WPB * WPB;
-  return (int)(w < WPB ? WPB : w);
+int blocks_for(long long n, int train) {
+  const long long groups = (n + 15) / 16, w = groups < MAXWAVES ? groups : MAXWAVES;
+  return (int)((w + wpb(train) - 1) / wpb(train));
 }
 
 igafd_status refresh(igafd_mlp* M) {
-  hipLaunchKernelGGL(k_mlp_refresh, dim3((NH * NH + 255) / 256), dim3(256), 0, M->stream, M->theta, M->w1b, M->w2b,
+  hipLaunchKernelGGL(k_mlp_refresh, dim3((NPARAM + 255) / 256), dim3(256), 0, M->stream, M->theta, M->w1b, M->w2b,
                      M->w2tb);
   IGAFD_HIP_CHECK(hipGetLastError());
   return IGAFD_OK;
 }
 
-igafd_status gradient(igafd_mlp* M, const float* feat, const float* target, long long n) {
-  const int nw = waves_for(n);
-  hipLaunchKernelGGL((k_mlp<1>), dim3(nw / WPB), dim3(kBlock), 0, M->stream, M->theta, M->w1b, M->w2b, M->w2tb,
-                     M->norm, feat, target, n, nullptr, nullptr, M->partial);
+// gradient and loss; with lr > 0 also the Adam step number `step`
+igafd_status gradient(igafd_mlp* M, const float* feat, const float* target, long long n, float lr, int step) {
+  const int nb = blocks_for(n, 1);
+  hipLaunchKernelGGL((k_mlp<1>), dim3(nb), dim3(64 * wpb(1)), 0, M->stream, M->theta, M->w1b, M->w2b, M->w2tb, M->norm,
+                     feat, target, n, nullptr, nullptr, M->partial);
   IGAFD_HIP_CHECK(hipGetLastError());
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + 1 + 255) / 256), dim3(256), 0, M->stream, M->partial, nw, M->grad,
-                     M->loss_dev, n);
+  const float c1 = 1.f - std::pow(0.9f, (float)step), c2 = 1.f - std::pow(0.999f, (float)step);
+  hipLaunchKernelGGL(k_mlp_step, dim3((NPARAM + kStepCols) / kStepCols), dim3(kStepCols * kStepRows), 0, M->stream,
+                     M->partial, nb, M->grad, M->loss_dev, n, lr, c1, c2, M->theta, M->adam_m, M->adam_v, M->w1b,
+                     M->w2b, M->w2tb);
   IGAFD_HIP_CHECK(hipGetLastError());
   return IGAFD_OK;
 }
@@ -350,7 +408,7 @@ igafd_status igafd_mlp_create(unsigned long long seed, void* stream, igafd_mlp**
     return IGAFD_ERR_ALLOC;                                         \
   }
   IGAFD_M(M->theta, pb) IGAFD_M(M->adam_m, pb) IGAFD_M(M->adam_v, pb) IGAFD_M(M->grad, pb)
-  IGAFD_M(M->partial, sizeof(float) * (size_t)MAXWAVES * (NPARAM + 1)) IGAFD_M(M->norm, sizeof(float) * 2 * NIN)
+  IGAFD_M(M->partial, sizeof(float) * (size_t)(MAXWAVES / wpb(1)) * (NPARAM + 1)) IGAFD_M(M->norm, sizeof(float) * 2 * NIN)
   IGAFD_M(M->w1b, sizeof(short) * NH * 16) IGAFD_M(M->w2b, sizeof(short) * NH * NH)
   IGAFD_M(M->w2tb, sizeof(short) * NH * NH) IGAFD_M(M->loss_dev, sizeof(float))
 #undef IGAFD_M
@@ -427,8 +485,7 @@ igafd_status igafd_mlp_forward(igafd_mlp* M, const float* feat, long long n, flo
     return IGAFD_ERR_ARG;
   }
   if (n == 0) return IGAFD_OK;
-  const int nw = waves_for(n);
-  hipLaunchKernelGGL((k_mlp<0>), dim3(nw / WPB), dim3(kBlock), 0, M->stream, M->theta, M->w1b, M->w2b, M->w2tb,
+  hipLaunchKernelGGL((k_mlp<0>), dim3(blocks_for(n, 0)), dim3(64 * wpb(0)), 0, M->stream, M->theta, M->w1b, M->w2b, M->w2tb,
                      M->norm, feat, nullptr, n, t_out, S_out, nullptr);
   IGAFD_HIP_CHECK(hipGetLastError());
   return IGAFD_OK;
@@ -440,7 +497,7 @@ igafd_status igafd_mlp_gradient(igafd_mlp* M, const float* feat, const float* ta
     set_error("bad arguments");
     return IGAFD_ERR_ARG;
   }
-  igafd_status s = gradient(M, feat, target, n);
+  igafd_status s = gradient(M, feat, target, n, 0.f, 1);
   if (s != IGAFD_OK) return s;
   IGAFD_HIP_CHECK(hipStreamSynchronize(M->stream));
   if (grad_host) IGAFD_HIP_CHECK(hipMemcpy(grad_host, M->grad, sizeof(float) * NPARAM, hipMemcpyDeviceToHost));
@@ -454,14 +511,9 @@ igafd_status igafd_mlp_train_step(igafd_mlp* M, const float* feat, const float* 
     set_error("bad arguments");
     return IGAFD_ERR_ARG;
   }
-  igafd_status s = gradient(M, feat, target, n);
+  igafd_status s = gradient(M, feat, target, n, lr, M->step + 1);
   if (s != IGAFD_OK) return s;
   M->step += 1;
-  const float c1 = 1.f - std::pow(0.9f, (float)M->step), c2 = 1.f - std::pow(0.999f, (float)M->step);
-  hipLaunchKernelGGL(k_mlp_adam, dim3((NPARAM + 255) / 256), dim3(256), 0, M->stream, M->theta, M->adam_m, M->adam_v,
-                     M->grad, lr, c1, c2);
-  IGAFD_HIP_CHECK(hipGetLastError());
-  if ((s = refresh(M)) != IGAFD_OK) return s;
   if (loss_host) {
     IGAFD_HIP_CHECK(hipMemcpyAsync(loss_host, M->loss_dev, sizeof(float), hipMemcpyDeviceToHost, M->stream));
     IGAFD_HIP_CHECK(hipStreamSynchronize(M->stream));
