@@ -680,15 +680,10 @@ igafd_status spmv_set_tile(igafd_ctx* c, int b2, int b3, int tb) {
     if (s != IGAFD_OK) return s;
   }
   if (need > c->ext_cap) {
-    if (c->ext) {
-      IGAFD_HIP_CHECK(hipStreamSynchronize(c->stream));
-      block_free(c->ext);
-    }
+    if (c->ext) IGAFD_HIP_CHECK(hipFree(c->ext));
     c->ext = nullptr;
     c->ext_cap = 0;
-    const igafd_status s = block_alloc((void**)&c->ext, sizeof(double) * (size_t)need);
-    if (s != IGAFD_OK) return s;
-    IGAFD_HIP_CHECK(hipMemsetAsync(c->ext, 0, sizeof(double) * (size_t)need, c->stream));
+    IGAFD_HIP_CHECK(hipMalloc((void**)&c->ext, sizeof(double) * (size_t)need));
     c->ext_cap = need;
   }
   c->tile_b2 = b2;
