@@ -1048,7 +1048,7 @@ igafd_status schwarz_apply(igafd_ctx* c, int prec, const double* r, double* s, c
 bool fd_fused_ok(const igafd_ctx* c) { return fused_ok(c) && !use_gemm(c, IGAFD_FP64); }
 
 int fd_dot_blocks(const igafd_ctx* c, int prec) {
-  if (c->adi) return (int)((c->N + kBlock - 1) / kBlock);
+  if (c->adi) return adi_dot_blocks(c);
   if (c->hole >= 0) return schwarz_blocks(c);
   if (use_gemm(c, prec)) return fd_gemm_blocks(c);
   return (c->fd_fused && fused_ok(c)) ? slice_blocks(c) : dot_blocks_for(c);

@@ -110,6 +110,7 @@ struct igafd_adi {
   double* bandK[3] = {nullptr, nullptr, nullptr};
   double* bandM[3] = {nullptr, nullptr, nullptr};
   double* fac[3] = {nullptr, nullptr, nullptr};
+  double* rows[3] = {nullptr, nullptr, nullptr};  // the same by rows over the diagonal (k_adi): per slot forward, backward
   double* bandKw1 = nullptr;  // K_1 - omega_j M_1 for every j: [J][n1][2p+1]
   double* work = nullptr;  // rt, v, u, t1, t2: 5 N doubles
 };
@@ -231,6 +232,7 @@ igafd_status adi_setup(igafd_ctx* c, double eps, int rule);
 igafd_status adi_apply(igafd_ctx* c, int prec, const double* r, double* s, const double* scaling,
                        double* partial_rz, const int* flag);
 void adi_free(igafd_ctx* c);
+int adi_dot_blocks(const igafd_ctx* c);
 // two independent 2D applies (no scaling, no partials) whose passes share launches
 igafd_status fd_apply_gemm2d_pair(int prec, igafd_ctx* c0, const double* r0, int ldr0, double* s0, int lds0,
                                   igafd_ctx* c1, const double* r1, int ldr1, double* s1, int lds1, const int* flag);
