@@ -10,10 +10,19 @@
 // four waves in a 2 x 2 grid, each TM x TN tiles of 16 x 16
 // (v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4).  Global loads run two slices
 // ahead: slice t+2 is loading while slice t feeds the MFMAs and slice t+1
-// goes from registers to LDS; loads use clamped (in-bounds) indices and the
-// values outside the matrices are zeroed only when they are stored to LDS,
-// so no load is waited for early.  Epilogue: division by lam_row[m] +
-// lam_col[n], the diagonal scalings of S P^-1 S, (r, s) block partials.
+// goes from registers to LDS.  The full slices' loads carry no condition: rows
+// and columns outside the matrices load clamped copies, whose results are not
+// stored, and only the last, partial slice is zeroed beyond K.  (With a
+// choice between vector and edge loads inside the loop the compiler could not
+// count the loads in flight and waited for all of them on every slice: products of
+// 1027^3 in FP32 65-76 us, of the L-shaped domain's 515 x 1030 pairs in split BF16
+// 47-58 us, of 513^4 in FP64 3.35-3.57 ms; without 49-51, 30-33 and 3.0 ms.  Tiles
+// of 32 x 64 and 32 x 32, with more blocks in flight, moved these by -8 to +20 %.)
+// FP64 products are bound by the MFMA rate and its 12 % padding to 64 (53 TFLOP/s of
+// the 73 that a large library product reaches here); the 2D ones by the slice's chain
+// of loads, LDS and MFMAs at one or two blocks per CU.
+// Epilogue: division by lam_row[m] + lam_col[n], the diagonal scalings of
+// S P^-1 S, (r, s) block partials.
 // Tiles go to the 8 XCDs in contiguous runs (blockIdx % 8 is the XCD), so
 // blocks that share an A row panel share an L2.
 //
@@ -23,6 +32,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include "internal.h"
 #include "reduce.h"
@@ -100,6 +110,11 @@ constexpr int kBK = 16;
 // LDS row padding (elements): the four lane groups of an MFMA operand read
 // four consecutive k-rows; a 16-element shift puts each group on its own banks
 constexpr int kPad = 16;
+// and kGap elements between groups of four k-rows, so that the transposing stores
+// (threads with k = 0, 4, 8, 12 side by side) spread over the banks too: without
+// them all four hit the same ones
+constexpr int kGap = 16;
+__host__ __device__ constexpr int k_row(int k, int ld) { return k * ld + (k >> 2) * kGap; }
 
 struct GEpi {
   const double* lrow = nullptr;  // with lcol: C[m][n] /= lrow[m] + lcol[n]
@@ -137,7 +152,7 @@ struct GProb {
 
 template <int TM, int TN, typename V>
 constexpr size_t lds_bytes() {
-  return sizeof(V) * 2 * kBK * ((2 * TM * 16 + kPad) + (2 * TN * 16 + kPad));
+  return sizeof(V) * 2 * (k_row(kBK, 2 * TM * 16 + kPad) + k_row(kBK, 2 * TN * 16 + kPad));
 }
 
 // N consecutive values from p (8- or 4-byte aligned), as V
@@ -188,8 +203,9 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   constexpr int APR = BK / EA;                                 // threads per row of the A slice
   constexpr int BPR = BT ? BK / EB : BN / EB;                  // threads per row of the stored B slice
   extern __shared__ __align__(16) unsigned char gsm[];
-  V* As = reinterpret_cast<V*>(gsm);  // [2][BK][LA]
-  V* Bs = As + 2 * BK * LA;           // [2][BK][LB]
+  constexpr int SA = k_row(BK, LA), SB = k_row(BK, LB);        // one slice in LDS
+  V* As = reinterpret_cast<V*>(gsm);  // [2][BK][LA], rows at k_row
+  V* Bs = As + 2 * SA;                // [2][BK][LB]
   if (ep.flag && *ep.flag) return;
   const int per = (ntiles + 7) / 8;
   const int tile = (bid & 7) * per + (bid >> 3);
@@ -207,50 +223,46 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   const int wm0 = (wave >> 1) * TM * 16, wn0 = (wave & 1) * TN * 16;
   const int ar = tid / APR, ak = (tid % APR) * EA;
   const int br = tid / BPR, bc = (tid % BPR) * EB;
-  // this thread's A row and (BT) Bm row, clamped into the matrices
+  // this thread's A row and (BT) Bm row or (NN) columns, clamped into the matrices:
+  // rows and columns of the tile outside them hold copies or stale values, which
+  // reach only results that are not stored
   const int am = tm0 + ar;
-  const bool am_ok = am < M;
-  const TA* arow = A + (long long)(am_ok ? am : M - 1) * lda;
-  const double* srow = PRE ? ep.Sa + (long long)(am_ok ? am : M - 1) * lda : nullptr;
+  const TA* arow = A + (long long)(am < M ? am : M - 1) * lda;
+  const double* srow = PRE ? ep.Sa + (long long)(am < M ? am : M - 1) * lda : nullptr;
   const int bn = BT ? tn0 + br : tn0 + bc;  // BT: row of Bm; else first column
-  const bool bn_ok = bn < N;
-  const TB* brow = BT ? B + (long long)(bn_ok ? bn : N - 1) * ldb : nullptr;
-  const bool bvec = !BT && bn + EB <= N;    // NN: this thread's EB columns all inside
+  const int bn0 = BT ? (bn < N ? bn : N - 1) : bn + EB <= N ? bn : N > EB ? N - EB : 0;
+  const TB* brow = BT ? B + (long long)bn0 * ldb : B + (long long)br * ldb + bn0;
+  const bool n_edge = !BT && tn0 + BN > N;
+  const bool narrow = !BT && N < EB;  // no EB columns to load as vectors
+  const int bcl = BT ? bc : bc - (bn - bn0);  // NN: the columns' place (overlapping copies in an edge tile)
 
   struct Stage {
     V a[EA], b[EB];
     double s[PRE ? EA : 1];
   };
+  // full slice: runs of consecutive k (A, BT) or n (NN) as vectors, no conditions,
+  // so that waiting for one slice leaves the next one's loads in flight
   auto load = [&](int k0, Stage& q) {
-    if (k0 + BK <= K) {  // full slice: runs of consecutive k (A, BT) or n (NN) as vectors
-      ldv<EA>(arow + k0 + ak, q.a);
-      if (PRE) ldv<EA>(srow + k0 + ak, q.s);
-      if (BT) {
-        ldv<EB>(brow + k0 + bc, q.b);
-      } else {
-        const TB* bp = B + (long long)(k0 + br) * ldb;
-        if (bvec) {
-          ldv<EB>(bp + bn, q.b);
-        } else {
+    ldv<EA>(arow + k0 + ak, q.a);
+    if (PRE) ldv<EA>(srow + k0 + ak, q.s);
+    if (BT)
+      ldv<EB>(brow + k0 + bc, q.b);
+    else
+      ldv<EB>(brow + (long long)k0 * ldb, q.b);
+  };
+  // any slice, value by value: the last one, K % BK deep, and those of narrow B
+  auto load_tail = [&](int k0, Stage& q) {
 #pragma unroll
-          for (int j = 0; j < EB; ++j) q.b[j] = (V)bp[bn + j < N ? bn + j : N - 1];
-        }
-      }
-    } else {
+    for (int j = 0; j < EA; ++j) {
+      const int k = k0 + ak + j < K ? k0 + ak + j : K - 1;
+      q.a[j] = (V)arow[k];
+      if (PRE) q.s[j] = srow[k];
+    }
 #pragma unroll
-      for (int j = 0; j < EA; ++j) {
-        const int k = k0 + ak + j < K ? k0 + ak + j : K - 1;
-        q.a[j] = (V)arow[k];
-        if (PRE) q.s[j] = srow[k];
-      }
-      if (BT) {
-#pragma unroll
-        for (int j = 0; j < EB; ++j) q.b[j] = (V)brow[k0 + bc + j < K ? k0 + bc + j : K - 1];
-      } else {
-        const TB* bp = B + (long long)(k0 + br < K ? k0 + br : K - 1) * ldb;
-#pragma unroll
-        for (int j = 0; j < EB; ++j) q.b[j] = (V)bp[bn + j < N ? bn + j : N - 1];
-      }
+    for (int j = 0; j < EB; ++j) {
+      const int k = BT ? k0 + bc + j : k0 + br;
+      const int kc = k < K ? k : K - 1;
+      q.b[j] = BT ? (V)brow[kc] : (V)brow[(long long)(kc - br) * ldb + (bn0 + j < N ? j : N - 1 - bn0)];
     }
   };
   // G16X3 splits each value once here, not in every wave that reads it: hi in
@@ -265,22 +277,36 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
       return v;
     }
   };
-  // zero what lies outside the matrices, then write the slice to LDS
-  auto store = [&](int buf, int k0, const Stage& q) {
-    V* as = As + buf * BK * LA;
-    V* bs = Bs + buf * BK * LB;
+  // write the slice to LDS; TAIL: zeros beyond K
+  auto store = [&](auto tail, int buf, int k0, const Stage& q) {
+    constexpr bool TAIL = decltype(tail)::value;
+    V* as = As + buf * SA;
+    V* bs = Bs + buf * SB;
 #pragma unroll
     for (int j = 0; j < EA; ++j) {
       V v = q.a[j];
       if (PRE) v = (V)((double)v * q.s[j]);
-      as[(ak + j) * LA + ar] = (am_ok && k0 + ak + j < K) ? lds_word(v) : V(0);
+      as[k_row(ak, LA) + k_row(j, LA) + ar] = !TAIL || k0 + ak + j < K ? lds_word(v) : V(0);
     }
+    V w[EB];
 #pragma unroll
-    for (int j = 0; j < EB; ++j) {
-      if (BT)
-        bs[(bc + j) * LB + br] = (bn_ok && k0 + bc + j < K) ? lds_word(q.b[j]) : V(0);
-      else
-        bs[br * LB + bc + j] = (k0 + br < K && bn + j < N) ? lds_word(q.b[j]) : V(0);
+    for (int j = 0; j < EB; ++j) w[j] = !TAIL || k0 + (BT ? bc + j : br) < K ? lds_word(q.b[j]) : V(0);
+    if (BT) {
+#pragma unroll
+      for (int j = 0; j < EB; ++j) bs[k_row(bc, LB) + k_row(j, LB) + br] = w[j];
+    } else if (!n_edge) {
+      constexpr int NV = 16 / sizeof(V);
+      typedef V vec_t __attribute__((ext_vector_type(NV)));
+#pragma unroll
+      for (int j = 0; j < EB; j += NV) {
+        vec_t x;
+#pragma unroll
+        for (int e = 0; e < NV; ++e) x[e] = w[j + e];
+        *reinterpret_cast<vec_t*>(bs + k_row(br, LB) + bc + j) = x;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < EB; ++j) bs[k_row(br, LB) + bcl + j] = w[j];
     }
   };
 
@@ -289,16 +315,18 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+  const bool off = tm0 + wm0 >= M || tn0 + wn0 >= N;  // this wave's part lies outside the matrix
   auto compute = [&](int buf) {
-    const V* as = As + buf * BK * LA;
-    const V* bs = Bs + buf * BK * LB;
+    if (off) return;
+    const V* as = As + buf * SA;
+    const V* bs = Bs + buf * SB;
     if constexpr (G::SPLIT) {
       gs4_t pa[TM], la[TM], pb[TN], lb[TN];
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const unsigned w = __float_as_uint(as[(grp + 4 * j) * LA + wm0 + i * 16 + col]);
+          const unsigned w = __float_as_uint(as[grp * LA + k_row(4 * j, LA) + wm0 + i * 16 + col]);
           pa[i][j] = (short)(w & 0xFFFFu);
           la[i][j] = (short)(w >> 16);
         }
@@ -306,7 +334,7 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
       for (int t = 0; t < TN; ++t)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const unsigned w = __float_as_uint(bs[(grp + 4 * j) * LB + wn0 + t * 16 + col]);
+          const unsigned w = __float_as_uint(bs[grp * LB + k_row(4 * j, LB) + wn0 + t * 16 + col]);
           pb[t][j] = (short)(w & 0xFFFFu);
           lb[t][j] = (short)(w >> 16);
         }
@@ -324,11 +352,11 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) pa[i][j] = bf16_bits(as[(grp + 4 * j) * LA + wm0 + i * 16 + col]);
+        for (int j = 0; j < 4; ++j) pa[i][j] = bf16_bits(as[grp * LA + k_row(4 * j, LA) + wm0 + i * 16 + col]);
 #pragma unroll
       for (int t = 0; t < TN; ++t)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) pb[t][j] = bf16_bits(bs[(grp + 4 * j) * LB + wn0 + t * 16 + col]);
+        for (int j = 0; j < 4; ++j) pb[t][j] = bf16_bits(bs[grp * LB + k_row(4 * j, LB) + wn0 + t * 16 + col]);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -340,9 +368,9 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
     for (int ks = 0; ks < BK; ks += 4) {
       V a[TM], b[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a[i] = as[(ks + grp) * LA + wm0 + i * 16 + col];
+      for (int i = 0; i < TM; ++i) a[i] = as[grp * LA + k_row(ks, LA) + wm0 + i * 16 + col];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) b[j] = bs[(ks + grp) * LB + wn0 + j * 16 + col];
+      for (int j = 0; j < TN; ++j) b[j] = bs[grp * LB + k_row(ks, LB) + wn0 + j * 16 + col];
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -350,25 +378,69 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
     }
   };
   // slice t is loaded into stage t & 1 and stored to LDS buffer t & 1
-  const int nk = (K + BK - 1) / BK;
+  const int nf = K / BK;  // full slices; a last one of K % BK rows
+  const bool tail = nf * BK < K;
+  const std::integral_constant<bool, false> kFull;
+  const std::integral_constant<bool, true> kTail;
   Stage q0, q1;
-  load(0, q0);
-  store(0, 0, q0);
-  if (nk > 1) load(BK, q1);
-  __syncthreads();
   // step t: load slice t+2 into stage t&1, compute slice t, store slice t+1
   auto step = [&](int t, Stage& ql, const Stage& qs) {
-    if (t + 2 < nk) load((t + 2) * BK, ql);
+    load((t + 2) * BK, ql);
+    __builtin_amdgcn_sched_barrier(0);  // issue the loads first
     compute(t & 1);
-    if (t + 1 < nk) store((t + 1) & 1, (t + 1) * BK, qs);
+    store(kFull, (t + 1) & 1, (t + 1) * BK, qs);
     __syncthreads();
   };
-  int t = 0;
-  for (; t + 1 < nk; t += 2) {
-    step(t, q0, q1);
-    step(t + 1, q1, q0);
+  // the last two full slices and the tail; ql, qs as in step
+  auto finish = [&](int t, Stage& ql, const Stage& qs) {  // t = nf - 2
+    if (tail) load_tail((t + 2) * BK, ql);
+    compute(t & 1);
+    store(kFull, (t + 1) & 1, (t + 1) * BK, qs);
+    __syncthreads();
+    compute((t + 1) & 1);
+    if (tail) {
+      store(kTail, t & 1, (t + 2) * BK, ql);
+      __syncthreads();
+      compute(t & 1);
+    }
+  };
+  if (narrow) {
+    for (int t = 0; t * BK < K; ++t) {
+      load_tail(t * BK, q0);
+      __syncthreads();
+      store(kTail, 0, t * BK, q0);
+      __syncthreads();
+      compute(0);
+    }
+  } else if (nf >= 2) {
+    load(0, q0);
+    load(BK, q1);
+    store(kFull, 0, 0, q0);
+    __syncthreads();
+    int t = 0;
+    for (; t + 3 < nf; t += 2) {
+      step(t, q0, q1);
+      step(t + 1, q1, q0);
+    }
+    if (t + 2 < nf) {
+      step(t, q0, q1);
+      finish(t + 1, q1, q0);
+    } else {
+      finish(t, q0, q1);
+    }
+  } else {
+    if (nf == 1) {
+      load(0, q0);
+      store(kFull, 0, 0, q0);
+    }
+    if (tail) {
+      load_tail(nf * BK, q1);
+      store(kTail, nf, nf * BK, q1);
+    }
+    __syncthreads();
+    if (nf == 1) compute(0);
+    if (tail) compute(nf);
   }
-  if (t < nk) step(t, q0, q1);
 
   double dot = 0.0;
 #pragma unroll
@@ -429,7 +501,7 @@ Cfg pick(int M, int N, int M1 = 0, int N1 = 0, int batch = 1) {
   Cfg best{2, 2};
   long long best_cost = -1, best_tiles = 0;
   for (const Cfg& g : cand) {
-    const size_t lds = sizeof(double) * 2 * kBK * ((2 * g.tm * 16 + kPad) + (2 * g.tn * 16 + kPad));
+    const size_t lds = sizeof(double) * 2 * (k_row(kBK, 2 * g.tm * 16 + kPad) + k_row(kBK, 2 * g.tn * 16 + kPad));
     if (lds > 64 * 1024) continue;
     long long tiles = (long long)batch * ((M + 32 * g.tm - 1) / (32 * g.tm)) * ((N + 32 * g.tn - 1) / (32 * g.tn));
     if (M1 > 0) tiles += (long long)((M1 + 32 * g.tm - 1) / (32 * g.tm)) * ((N1 + 32 * g.tn - 1) / (32 * g.tn));
