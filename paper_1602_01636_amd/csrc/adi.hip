@@ -951,8 +951,8 @@ igafd_status adi_setup(igafd_ctx* c, double eps, int rule) {
       set_error("band Cholesky of K_d + omega M_d failed");
       return IGAFD_ERR_NOT_SPD;
     }
-    IGAFD_HIP_CHECK(hipMalloc((void**)&st->bandK[d], sizeof(double) * bK.size()));
-    IGAFD_HIP_CHECK(hipMalloc((void**)&st->bandM[d], sizeof(double) * bM.size()));
+    IGAFD_HIP_CHECK(device_malloc((void**)&st->bandK[d], sizeof(double) * bK.size()));
+    IGAFD_HIP_CHECK(device_malloc((void**)&st->bandM[d], sizeof(double) * bM.size()));
     // the sweeps' rows (adi_sweep): forward 1/L_ii, L_{i+k,i}/L_{i+k,i+k}; backward, i from
     // the end after the zero rows, 1/L_ii, L_{i,i-k}/L_{i-k,i-k}
     const int RP = even_up(WL), R = adi_rows(n);
@@ -968,9 +968,9 @@ igafd_status adi_setup(igafd_ctx* c, double eps, int rule) {
           if (i - k >= 0) bw[k] = f[(size_t)i * WL + k] * f[(size_t)(i - k) * WL];
         }
       }
-    IGAFD_HIP_CHECK(hipMalloc((void**)&st->rows[d], sizeof(double) * rows.size()));
+    IGAFD_HIP_CHECK(device_malloc((void**)&st->rows[d], sizeof(double) * rows.size()));
     IGAFD_HIP_CHECK(hipMemcpy(st->rows[d], rows.data(), sizeof(double) * rows.size(), hipMemcpyHostToDevice));
-    IGAFD_HIP_CHECK(hipMalloc((void**)&st->fac[d], sizeof(double) * fac.size()));
+    IGAFD_HIP_CHECK(device_malloc((void**)&st->fac[d], sizeof(double) * fac.size()));
     IGAFD_HIP_CHECK(hipMemcpy(st->bandK[d], bK.data(), sizeof(double) * bK.size(), hipMemcpyHostToDevice));
     IGAFD_HIP_CHECK(hipMemcpy(st->bandM[d], bM.data(), sizeof(double) * bM.size(), hipMemcpyHostToDevice));
     IGAFD_HIP_CHECK(hipMemcpy(st->fac[d], fac.data(), sizeof(double) * fac.size(), hipMemcpyHostToDevice));
@@ -981,10 +981,10 @@ igafd_status adi_setup(igafd_ctx* c, double eps, int rule) {
     std::vector<double> kw((size_t)J * n * W);
     for (int j = 0; j < J; ++j)
       for (size_t e = 0; e < bK.size(); ++e) kw[(size_t)j * n * W + e] = bK[e] - w[j] * bM[e];
-    IGAFD_HIP_CHECK(hipMalloc((void**)&st->bandKw1, sizeof(double) * kw.size()));
+    IGAFD_HIP_CHECK(device_malloc((void**)&st->bandKw1, sizeof(double) * kw.size()));
     IGAFD_HIP_CHECK(hipMemcpy(st->bandKw1, kw.data(), sizeof(double) * kw.size(), hipMemcpyHostToDevice));
   }
-  IGAFD_HIP_CHECK(hipMalloc((void**)&st->work, sizeof(double) * 5 * (size_t)c->N));
+  IGAFD_HIP_CHECK(device_malloc((void**)&st->work, sizeof(double) * 5 * (size_t)c->N));
   igafd_status sa = adi_lds_attr(c);
   if (sa != IGAFD_OK) return sa;
   adi_free(c);

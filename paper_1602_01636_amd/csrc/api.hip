@@ -75,6 +75,35 @@ void trim_blocks(int device, size_t keep, long long oldest) {  // under the mute
 }
 }  // namespace
 
+// the cached blocks of the current device go back to the driver
+static void drop_blocks() {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return;
+  std::lock_guard<std::mutex> lock(g_block_mutex);
+  trim_blocks(device, 0, g_block_clock - kCacheAge);
+}
+
+hipError_t device_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    drop_blocks();
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
+// a tile shape whose buffer found no room is tried once more without the cache
+static igafd_status set_tile(igafd_ctx* c, int b2, int b3, int tb) {
+  igafd_status s = spmv_set_tile(c, b2, b3, tb);
+  if (s == IGAFD_ERR_HIP) {
+    (void)hipGetLastError();
+    drop_blocks();
+    s = spmv_set_tile(c, b2, b3, tb);
+  }
+  return s;
+}
+
 igafd_status block_alloc(void** p, size_t bytes) {
   *p = nullptr;
   int device = 0;
@@ -98,13 +127,7 @@ igafd_status block_alloc(void** p, size_t bytes) {
     trim_blocks(device, kCacheBytes, g_block_clock - kCacheAge);
     if (*p) return IGAFD_OK;
   }
-  hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    std::lock_guard<std::mutex> lock(g_block_mutex);
-    trim_blocks(device, 0, g_block_clock - kCacheAge);
-    e = hipMalloc(p, bytes);
-  }
+  const hipError_t e = device_malloc(p, bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
@@ -408,7 +431,7 @@ unsigned vblocks(const igafd_ctx* c) { return (unsigned)((c->N + kBlock - 1) / k
 
 template <typename T>
 igafd_status dev_upload(T** dst, const T* src, size_t count, hipStream_t st) {
-  IGAFD_HIP_CHECK(hipMalloc((void**)dst, sizeof(T) * (count ? count : 1)));
+  IGAFD_HIP_CHECK(device_malloc((void**)dst, sizeof(T) * (count ? count : 1)));
   if (count) IGAFD_HIP_CHECK(hipMemcpyAsync(*dst, src, sizeof(T) * count, hipMemcpyHostToDevice, st));
   return IGAFD_OK;
 }
@@ -654,15 +677,15 @@ igafd_status alloc_workspace(igafd_ctx* c) {
   // partial sums: one (or two) per block of every reduction kernel, for any
   // kernel shape the autotuner may pick
   c->npartial = partial_capacity(c);
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->partial, sizeof(double) * 2 * (size_t)c->npartial));
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->state, sizeof(SolverState)));
+  IGAFD_HIP_CHECK(device_malloc((void**)&c->partial, sizeof(double) * 2 * (size_t)c->npartial));
+  IGAFD_HIP_CHECK(device_malloc((void**)&c->state, sizeof(SolverState)));
   IGAFD_HIP_CHECK(hipHostMalloc((void**)&c->hstate, sizeof(SolverState), hipHostMallocDefault));
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->dflag, sizeof(int)));
+  IGAFD_HIP_CHECK(device_malloc((void**)&c->dflag, sizeof(int)));
   IGAFD_HIP_CHECK(hipEventCreate(&c->ev0));
   IGAFD_HIP_CHECK(hipEventCreate(&c->ev1));
   // residual history for the default iteration budget (maxit 2000 + the start)
   c->hist_alloc = kHistDefault;
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->hist, sizeof(double) * c->hist_alloc));
+  IGAFD_HIP_CHECK(device_malloc((void**)&c->hist, sizeof(double) * c->hist_alloc));
   return IGAFD_OK;
 }
 
@@ -845,7 +868,7 @@ igafd_status solve_impl(igafd_ctx* c, const double* b, double* x, const igafd_so
     if (c->hist) IGAFD_HIP_CHECK(hipFree(c->hist));
     c->hist = nullptr;
     c->hist_alloc = 0;
-    IGAFD_HIP_CHECK(hipMalloc((void**)&c->hist, sizeof(double) * hcap));
+    IGAFD_HIP_CHECK(device_malloc((void**)&c->hist, sizeof(double) * hcap));
     c->hist_alloc = hcap;
   }
   if (hcap) hist = c->hist;
@@ -980,7 +1003,7 @@ igafd_status GroupArena::upload(hipStream_t st) {
     if (dev) IGAFD_HIP_CHECK(hipFree(dev));
     dev = nullptr;
     cap = 0;
-    IGAFD_HIP_CHECK(hipMalloc((void**)&dev, host.size()));
+    IGAFD_HIP_CHECK(device_malloc((void**)&dev, host.size()));
     cap = host.size();
   }
   IGAFD_HIP_CHECK(hipMemcpyAsync(dev, host.data(), host.size(), hipMemcpyHostToDevice, st));
@@ -1377,7 +1400,7 @@ igafd_status solve_batched_impl(igafd_ctx* const* cs, int count, const double* c
   // init: r = b, x = 0, ||b||, ||r||; then the first directions
   std::vector<int> hflags(count, 0);
   if (grouped) {
-    IGAFD_BH(hipMalloc((void**)&dflags, sizeof(int) * count));
+    IGAFD_BH(device_malloc((void**)&dflags, sizeof(int) * count));
     std::vector<int> all(count);
     for (int i = 0; i < count; ++i) all[i] = i;
     std::vector<GroupStep> ph;
@@ -1665,7 +1688,7 @@ igafd_status autotune_impl(igafd_ctx* c, int reps) {
   Cand best_c{c->spmv_rows, c->tile_b2, c->tile_b3, c->tile_tb};
   for (const Cand& k : cands) {
     c->spmv_rows = k.rows;
-    if (spmv_set_tile(c, k.b2, k.b3, k.tb) != IGAFD_OK) continue;
+    if (set_tile(c, k.b2, k.b3, k.tb) != IGAFD_OK) continue;
     bool ok = true;
     const float ms = time_it([&]() { ok = ok && spmv(c, c->pv, c->q, nullptr, nullptr) == IGAFD_OK; });
     // a later candidate must be 1% faster: near-ties keep the earlier one, so
@@ -1676,7 +1699,7 @@ igafd_status autotune_impl(igafd_ctx* c, int reps) {
     }
   }
   c->spmv_rows = best_c.rows;
-  IGAFD_TRY(spmv_set_tile(c, best_c.b2, best_c.b3, best_c.tb));
+  IGAFD_TRY(set_tile(c, best_c.b2, best_c.b3, best_c.tb));
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
   IGAFD_HIP_CHECK(hipGetLastError());
@@ -1752,7 +1775,7 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
     // preconditioner's (r, s) product and of the spectral bounds
     if ((s = alloc_scratch(c.get(), {&c->fdbuf[0], &c->fdbuf[1]})) != IGAFD_OK) return s;
     c->npartial = partial_capacity(c.get());
-    IGAFD_HIP_CHECK(hipMalloc((void**)&c->partial, sizeof(double) * 2 * (size_t)c->npartial));
+    IGAFD_HIP_CHECK(device_malloc((void**)&c->partial, sizeof(double) * 2 * (size_t)c->npartial));
     if ((s = eigen()) != IGAFD_OK) return s;
     IGAFD_HIP_CHECK(hipStreamSynchronize(c->stream));
     c->t_setup_ms = elapsed_ms(t_start);
@@ -1785,7 +1808,7 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
         tb = 512;
       }
     }
-    if ((s = spmv_set_tile(c.get(), b2, b3, tb)) != IGAFD_OK) return s;
+    if ((s = set_tile(c.get(), b2, b3, tb)) != IGAFD_OK) return s;
   }
   // the device assembles A while the host computes the eigendecompositions
   AsmWork work{nullptr, c->stream};

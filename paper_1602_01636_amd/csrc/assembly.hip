@@ -1559,7 +1559,7 @@ igafd_status setup_modes(igafd_ctx* c) {
   const int K = mode_count(c);
   if (K == 0) return IGAFD_OK;
   const int nq[3] = {c->dir[0].nel * c->dir[0].q, c->dir[1].nel * c->dir[1].q, c->dir[2].nel * c->dir[2].q};
-  IGAFD_HIP_CHECK(hipMalloc((void**)&c->modes, sizeof(double) * K * (2 * (size_t)nq[0] + 2 * (size_t)nq[1] + 6 * (size_t)nq[2])));
+  IGAFD_HIP_CHECK(device_malloc((void**)&c->modes, sizeof(double) * K * (2 * (size_t)nq[0] + 2 * (size_t)nq[1] + 6 * (size_t)nq[2])));
   const Modes m = modes_of(c);
   double *d0 = const_cast<double*>(m.d12[0]), *d1 = const_cast<double*>(m.d12[1]), *d3 = const_cast<double*>(m.d3);
   const dim3 grid((unsigned)cdiv((long long)(nq[0] + nq[1] + nq[2]) * K, 128));
@@ -1679,7 +1679,7 @@ igafd_status features(igafd_ctx* c, float* feat) {
     return IGAFD_OK;
   }
   double* acc = nullptr;
-  IGAFD_HIP_CHECK(hipMalloc((void**)&acc, sizeof(double) * 8 * (size_t)c->N));
+  IGAFD_HIP_CHECK(device_malloc((void**)&acc, sizeof(double) * 8 * (size_t)c->N));
   igafd_status st = features_into(c, acc, feat);
   (void)hipStreamSynchronize(c->stream);
   (void)hipFree(acc);

@@ -30,6 +30,7 @@ constexpr long long kTile512Lds = 128 * 1024;
 void set_error(const std::string& msg);
 // large device blocks, recycled between contexts (api.hip)
 igafd_status block_alloc(void** p, size_t bytes);
+hipError_t device_malloc(void** p, size_t bytes);  // hipMalloc; where that fails, again without the recycled blocks
 void block_free(void* p);
 // block partials (per sum) a context's reductions may write; sizes its buffer
 int partial_capacity(const igafd_ctx* c);

@@ -402,7 +402,7 @@ igafd_status igafd_mlp_create(unsigned long long seed, void* stream, igafd_mlp**
   *out = nullptr;
   const size_t pb = sizeof(float) * NPARAM;
 #define IGAFD_M(ptr, bytes)                                         \
-  if (hipMalloc((void**)&(ptr), (bytes)) != hipSuccess) {           \
+  if (device_malloc((void**)&(ptr), (bytes)) != hipSuccess) {           \
     igafd_mlp_destroy(M);                                           \
     set_error("allocation of the network buffers failed");          \
     return IGAFD_ERR_ALLOC;                                         \
