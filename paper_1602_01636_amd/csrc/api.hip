@@ -141,7 +141,23 @@ igafd_status block_alloc(void** p, size_t bytes) {
   return IGAFD_OK;
 }
 
-void block_free(void* p) {
+// Waits for a stream of a device, which need not be the current one (the null
+// stream is each device's own).  A stream that its owner has destroyed leaves
+// only the device to wait for.
+bool wait_stream(hipStream_t stream, int device) {
+  int current = device;
+  (void)hipGetDevice(&current);
+  if (current != device && hipSetDevice(device) != hipSuccess) return false;
+  hipError_t e = hipStreamSynchronize(stream);
+  if (e != hipSuccess) {
+    e = hipDeviceSynchronize();
+    (void)hipGetLastError();  // the failed wait is no later call's error
+  }
+  if (current != device) (void)hipSetDevice(current);
+  return e == hipSuccess;
+}
+
+void block_free(void* p, bool idle) {
   if (!p) return;
   {
     std::lock_guard<std::mutex> lock(g_block_mutex);
@@ -149,6 +165,10 @@ void block_free(void* p) {
     if (it != g_blocks.end()) {
       Block b = it->second;
       g_blocks.erase(it);
+      if (!idle) {
+        (void)hipFree(p);
+        return;
+      }
       b.stamp = g_block_clock;
       g_cached.push_back(b);
       trim_blocks(b.device, kCacheBytes, g_block_clock - kCacheAge);
@@ -425,7 +445,9 @@ __global__ __launch_bounds__(kBlock) void k_residual(const double* __restrict__ 
   if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
-void free_dev(void* p) { block_free(p); }
+void free_dev(void* p) {
+  if (p) (void)hipFree(p);
+}
 
 unsigned vblocks(const igafd_ctx* c) { return (unsigned)((c->N + kBlock - 1) / kBlock); }
 
@@ -570,6 +592,7 @@ igafd_status create_fd_sub(int p, const Dir1D& d1, const Dir1D& d2, hipStream_t 
   c->dim = 2;
   c->p = p;
   c->stream = st;
+  IGAFD_HIP_CHECK(hipGetDevice(&c->device));
   c->N = 1;
   c->dir[0] = d1;
   c->dir[1] = d2;
@@ -1811,7 +1834,7 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
     if ((s = set_tile(c.get(), b2, b3, tb)) != IGAFD_OK) return s;
   }
   // the device assembles A while the host computes the eigendecompositions
-  AsmWork work{nullptr, c->stream};
+  AsmWork work{nullptr, c.get()};
   s = assemble_band(c.get(), pr->want_features != 0, &work);
   const igafd_status se = s == IGAFD_OK ? eigen() : s;
   if (se != IGAFD_OK) return se;
@@ -1843,16 +1866,13 @@ igafd_status igafd_univariate(int degree, int nknots, const double* knots, int q
 
 void igafd_destroy(igafd_ctx* c) {
   if (!c) return;
-  (void)hipStreamSynchronize(c->stream);  // its blocks may go to another context and stream
+  const bool idle = wait_stream(c->stream, c->device);  // its blocks may go to another context and stream
   for (int k = 0; k < 2; ++k) igafd_destroy(c->sub[k]);
   adi_free(c);
   for (int l = 0; l < 3; ++l) free_dir(&c->ddir[l]);
-  free_dev(c->band);
+  for (double* b : {c->band, c->scratch, c->pv_pad, c->xpad, c->scaling}) block_free(b, idle);
+  block_free(c->feat, idle);
   free_dev(c->ext);
-  free_dev(c->scratch);
-  free_dev(c->pv_pad);
-  free_dev(c->xpad);
-  free_dev(c->scaling);
   free_dev(c->partial);
   free_dev(c->state);
   free_dev(c->dflag);
@@ -1860,7 +1880,6 @@ void igafd_destroy(igafd_ctx* c) {
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   free_dev(c->hist);
-  free_dev(c->feat);
   free_dev(c->modes);
   for (hipEvent_t e : c->tev) (void)hipEventDestroy(e);
   delete c;

@@ -1576,9 +1576,7 @@ long long load_scratch(const igafd_ctx* c) {  // 3D: the moments of one plane i3
 }
 
 AsmWork::~AsmWork() {
-  if (!ws) return;
-  (void)hipStreamSynchronize(stream);
-  block_free(ws);
+  if (ws) block_free(ws, wait_stream(c->stream, c->device));
 }
 
 igafd_status assemble_band(igafd_ctx* c, bool with_features, AsmWork* work) {

@@ -31,7 +31,9 @@ void set_error(const std::string& msg);
 // large device blocks, recycled between contexts (api.hip)
 igafd_status block_alloc(void** p, size_t bytes);
 hipError_t device_malloc(void** p, size_t bytes);  // hipMalloc; where that fails, again without the recycled blocks
-void block_free(void* p);
+// idle: everything that used the block has finished (else it goes to the driver)
+void block_free(void* p, bool idle = true);
+bool wait_stream(hipStream_t stream, int device);  // false: could not be waited for
 // block partials (per sum) a context's reductions may write; sizes its buffer
 int partial_capacity(const igafd_ctx* c);
 
@@ -191,7 +193,7 @@ long long load_scratch(const igafd_ctx* c);  // doubles that a load vector needs
 // workspace that is released once the stream has passed it
 struct AsmWork {
   double* ws;
-  hipStream_t stream;
+  const igafd_ctx* c;
   ~AsmWork();
 };
 igafd_status assemble_band(igafd_ctx* c, bool with_features, AsmWork* work);
