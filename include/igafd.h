@@ -27,10 +27,13 @@
  *    ABI.  igafd_last_error() gives a thread-local message for the last
  *    non-OK status.  A status > 0 is a warning with results written.
  *  - The context owns every device allocation it makes (matrix band,
- *    eigenvector copies, workspace); igafd_destroy releases them: blocks of
- *    1 MiB or more to a cache of at most 8 GiB per device that later contexts
- *    take them from (returned to the driver when unused for a while or when
- *    an allocation fails), the others to the driver.
+ *    eigenvector copies, workspace); igafd_destroy releases them: its large
+ *    buffers (1 MiB or more) to a cache of at most 8 GiB per device that later
+ *    contexts take them from, the others to the driver.  A cached buffer goes
+ *    to the driver when 64 later requests for large buffers found no use for
+ *    it, when the bound is exceeded, when an allocation of this library fails,
+ *    or by igafd_release_cached.  It does not age with time: a program that is
+ *    done with its contexts and wants the memory for something else calls that.
  */
 #ifndef IGAFD_H
 #define IGAFD_H
@@ -407,6 +410,9 @@ igafd_status igafd_mlp_train_step(igafd_mlp* mlp, const float* feat_dev, const f
                                   float lr, float* loss_host);
 
 void igafd_destroy(igafd_ctx* ctx);
+/* Returns the buffers kept from destroyed contexts, on every device, to the
+ * driver.  Result: their bytes.  Live contexts are not touched. */
+long long igafd_release_cached(void);
 const char* igafd_last_error(void);
 
 #ifdef __cplusplus

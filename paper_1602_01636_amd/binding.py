@@ -81,6 +81,7 @@ _SIGNATURES = {
     "igafd_univariate": (C.c_int, [C.c_int, C.c_int, C.POINTER(C.c_double), C.c_int, C.c_void_p, C.c_void_p,
                                    C.c_void_p, C.c_void_p, C.POINTER(C.c_int)]),
     "igafd_destroy": (None, [C.c_void_p]),
+    "igafd_release_cached": (C.c_longlong, []),
     "igafd_last_error": (C.c_char_p, []),
     "igafd_features": (C.c_int, [C.c_void_p, C.c_void_p]),
     "igafd_features_noalloc": (C.c_int, [C.c_void_p, C.c_void_p]),
@@ -452,6 +453,12 @@ def igafd_destroy(ctx):
         ctx.close()
     elif ctx:
         lib().igafd_destroy(ctx)
+
+
+def igafd_release_cached() -> int:
+    """Returns the device buffers kept from destroyed contexts to the driver
+    (for torch or another library to use); the number of bytes."""
+    return lib().igafd_release_cached()
 
 
 # ---------------- learned diagonal scaling ----------------

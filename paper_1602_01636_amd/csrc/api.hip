@@ -42,8 +42,10 @@ void set_error(const std::string& msg) { g_err = msg; }
 // problem whose setup takes 20.  Bounds: kCacheBytes per device; a block is
 // reused for requests of at least 4/5 of its size, and given back to the
 // driver when kCacheAge later requests found no use for it, when the bound is
-// exceeded (oldest first), or when an allocation fails.  Callers release a
-// block only after the work that used it has finished.
+// exceeded (oldest first), when an allocation of this library fails, or by
+// igafd_release_cached (a process that makes no further request keeps its
+// blocks until it calls that).  Callers release a block only after the work
+// that used it has finished.
 namespace {
 constexpr size_t kCacheMin = 1u << 20, kCacheBytes = (size_t)8 << 30;
 constexpr long long kCacheAge = 64;
@@ -1862,6 +1864,17 @@ igafd_status igafd_univariate(int degree, int nknots, const double* knots, int q
   if (U) std::memcpy(U, d.U.data(), sizeof(double) * d.U.size());
   if (lam) std::memcpy(lam, d.lam.data(), sizeof(double) * d.lam.size());
   return IGAFD_OK;
+}
+
+long long igafd_release_cached(void) {
+  std::lock_guard<std::mutex> lock(g_block_mutex);
+  long long bytes = 0;
+  for (const Block& b : g_cached) {
+    (void)hipFree(b.p);
+    bytes += (long long)b.bytes;
+  }
+  g_cached.clear();
+  return bytes;
 }
 
 void igafd_destroy(igafd_ctx* c) {

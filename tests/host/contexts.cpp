@@ -6,7 +6,7 @@
 #include <vector>
 
 #include "hip_double.h"
-#include "igafd.h"
+#include "internal.h"
 
 #define CHECK(x)                                             \
   do {                                                       \
@@ -91,6 +91,107 @@ int destroyed_stream() {
   return 0;
 }
 
+constexpr size_t kMiB = 1 << 20, kGiB = (size_t)1 << 30;
+
+void* take(size_t bytes) {
+  void* p = nullptr;
+  return igafd::block_alloc(&p, bytes) == IGAFD_OK ? p : nullptr;
+}
+
+// Reuse: by device, for requests of 4/5 of a block and more, the smallest such
+// block first; small blocks are not kept.
+int cache_fit() {
+  void* a = take(100 * kMiB);
+  void* b = take(90 * kMiB);
+  CHECK(a && b);
+  igafd::block_free(a);
+  igafd::block_free(b);
+  CHECK(hip_double::frees == 0);
+  CHECK(take(80 * kMiB) == b);
+  CHECK(take(80 * kMiB) == a);
+  igafd::block_free(a);
+  void* c = take(79 * kMiB);  // below 4/5
+  CHECK(c && c != a);
+  CHECK(take(101 * kMiB) != a);
+  CHECK(hipSetDevice(1) == hipSuccess);
+  void* d = take(100 * kMiB);
+  CHECK(d != a && hip_double::bytes_on(1) == 100 * kMiB);
+  igafd::block_free(d);  // freed from any device, reused on its own
+  CHECK(hipSetDevice(0) == hipSuccess);
+  CHECK(take(100 * kMiB) == a);
+  CHECK(take(100 * kMiB) != d);
+  void* s = take(kMiB - 1);
+  const long long frees = hip_double::frees;
+  igafd::block_free(s);
+  CHECK(hip_double::frees == frees + 1);
+  return 0;
+}
+
+// At most 8 GiB per device, the oldest given back first; blocks without use
+// for 64 later requests are given back.
+int cache_bound_and_age() {
+  void* p[6];
+  for (int d = 0; d < 2; ++d) {
+    CHECK(hipSetDevice(d) == hipSuccess);
+    for (void*& q : p) CHECK((q = take(2 * kGiB)) != nullptr);
+    for (void* q : p) igafd::block_free(q);
+    CHECK(hip_double::bytes_on(d) == 8 * kGiB);
+    CHECK(hip_double::bytes_on(0) == 8 * kGiB);  // the other device's are its own
+  }
+  CHECK(hip_double::live.count(p[5]) == 1 && hip_double::live.count(p[2]) == 1);
+  CHECK(hip_double::live.count(p[1]) == 0 && hip_double::live.count(p[0]) == 0);
+  void* big = take(9 * kGiB);  // larger than the bound: never kept
+  igafd::block_free(big);
+  CHECK(hip_double::live.count(big) == 0);
+  CHECK(igafd_release_cached() >= 0 && hip_double::bytes_on(0) == 0 && hip_double::bytes_on(1) == 0);
+  void* old = take(32 * kMiB);
+  igafd::block_free(old);
+  for (int k = 0; k < 64; ++k) {
+    void* q = take(2 * kMiB);
+    CHECK(q && hip_double::live.count(old) == 1);
+    igafd::block_free(q);
+  }
+  void* q = take(2 * kMiB);
+  CHECK(q && hip_double::live.count(old) == 0);
+  return 0;
+}
+
+// An allocation that fails is made again without the cached blocks, whatever it is for.
+int cache_failed_allocation() {
+  void* a = take(6 * kGiB);
+  igafd::block_free(a);
+  hip_double::capacity = 10 * kGiB;
+  void* b = take(8 * kGiB);
+  CHECK(b && hip_double::bytes_on(0) == 8 * kGiB);
+  igafd::block_free(b);
+  void* c = nullptr;
+  CHECK(igafd::device_malloc(&c, 9 * kGiB) == hipSuccess && hip_double::bytes_on(0) == 9 * kGiB);
+  CHECK(hipGetLastError() == hipSuccess);
+  CHECK(!take(2 * kGiB));
+  CHECK(std::string(igafd_last_error()).find("device allocation") != std::string::npos);
+  CHECK(hipGetLastError() == hipSuccess);
+  return 0;
+}
+
+// igafd_release_cached gives everything back that no context holds, and nothing else.
+int cache_release() {
+  igafd_ctx* live = setup(40, 3, nullptr, true);
+  CHECK(live);
+  const size_t held = hip_double::bytes_on(0);
+  igafd_ctx* c = setup(40, 3, nullptr, true);
+  CHECK(c);
+  igafd_destroy(c);
+  const size_t kept = hip_double::bytes_on(0) - held;
+  CHECK(kept > 0 && kept <= 8 * kGiB);
+  CHECK(igafd_release_cached() > 0);
+  CHECK(hip_double::bytes_on(0) <= held);
+  CHECK(igafd_release_cached() == 0);
+  igafd_destroy(live);
+  CHECK(igafd_release_cached() > 0);
+  CHECK(hip_double::bytes_on(0) == 0 && hip_double::live.empty());
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -98,6 +199,10 @@ int main(int argc, char** argv) {
   int bad = 1;
   if (what == "destroy_waits") bad = destroy_waits();
   if (what == "destroyed_stream") bad = destroyed_stream();
+  if (what == "cache_fit") bad = cache_fit();
+  if (what == "cache_bound_and_age") bad = cache_bound_and_age();
+  if (what == "cache_failed_allocation") bad = cache_failed_allocation();
+  if (what == "cache_release") bad = cache_release();
   if (!bad) std::printf("OK\n");
   std::fflush(stdout);
   return bad;

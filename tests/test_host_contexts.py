@@ -35,3 +35,14 @@ def _check(exe, what):
 @pytest.mark.parametrize("what", ["destroy_waits", "destroyed_stream"])
 def test_memory_is_handed_on_after_its_stream(contexts, what):
     _check(contexts, what)
+
+
+@pytest.mark.parametrize("what", ["cache_fit", "cache_bound_and_age", "cache_failed_allocation", "cache_release"])
+def test_block_cache(contexts, what):
+    _check(contexts, what)
+
+
+def test_release_is_bound():
+    import paper_1602_01636_amd as api
+    assert api.igafd_release_cached() >= 0
+    assert api.igafd_release_cached() == 0
