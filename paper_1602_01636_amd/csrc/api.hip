@@ -529,7 +529,10 @@ igafd_status eigen_all(const std::vector<Dir1D*>& dirs) {
     for (size_t j = 0; j < i && same[i] == (int)i; ++j)
       if (dirs[j]->p == dirs[i]->p && dirs[j]->q == dirs[i]->q && dirs[j]->knots == dirs[i]->knots) same[i] = (int)j;
   }
-  auto run = [&](size_t i) { st[i] = eigen_direction(dirs[i]); };
+  int distinct = 0;
+  for (size_t i = 0; i < dirs.size(); ++i) distinct += same[i] == (int)i;
+  const int team_max = eigen_threads(distinct);
+  auto run = [&](size_t i) { st[i] = eigen_direction(dirs[i], team_max); };
   for (size_t i = 1; i < dirs.size(); ++i) {
     if (same[i] != (int)i) continue;
     try {

@@ -72,7 +72,9 @@ struct Dir1D {
 // eig = false: element tables and M, K only (no eigendecomposition)
 igafd_status build_direction(int p, int q, int nknots, const double* knots, Dir1D* out, bool eig = true);
 
-igafd_status eigen_direction(Dir1D* d);  // U and lam of a direction built without them
+// U and lam of a direction built without them; team_max: the most threads of its team
+igafd_status eigen_direction(Dir1D* d, int team_max);
+int eigen_threads(int concurrent);  // team_max of each of several decompositions at once
 
 // Device copies of one direction.
 struct DevDir {

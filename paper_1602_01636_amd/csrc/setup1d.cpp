@@ -18,6 +18,16 @@
 
 namespace igafd {
 
+// A team's threads spin at two barriers per reflector, so the decompositions
+// that run at once share one budget of 16 team threads (or the CPUs, if fewer).
+// Setups on 16 CPUs with 16 for each and with 16 in all: three directions of
+// n = 620-640 150 and 128 ms, two of 1000 400 and 335 ms, two of 1500-1600 1.1
+// and 1.2 s; one team at a time 260 ms, 515 ms and 1.45 s.
+int eigen_threads(int concurrent) {
+  const int all = std::min(16, (int)std::thread::hardware_concurrency());
+  return std::max(1, all / std::max(1, concurrent));
+}
+
 namespace {
 
 // Legendre polynomials P_q(z) and P_{q-1}(z) by the three-term recurrence.
@@ -97,9 +107,7 @@ void span_basis(const double* t, int p, int k, double x, double* N, double* dN) 
 // (serially when n < 2 * min_chunk).
 template <class F>
 void parallel_rows(int n, int min_chunk, const F& fn) {
-  const unsigned hw = std::thread::hardware_concurrency();
-  const int T = (int)std::max(1u, std::min(16u, hw));
-  const int chunks = std::min(T, n / std::max(1, min_chunk));
+  const int chunks = std::min(eigen_threads(1), n / std::max(1, min_chunk));
   if (chunks <= 1) {
     fn(0, n);
     return;
@@ -233,8 +241,9 @@ void forward_rows(const std::vector<double>& L, int n, int bw, std::vector<doubl
 // S (n x n, row-major) is destroyed; on return lam holds the eigenvalues in
 // ascending order and V the orthonormal eigenvectors as columns (V[i][k]).
 // The QR steps run on the tridiagonal alone; their plane rotations are
-// recorded and applied to V afterwards, a block of rows at a time.
-void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std::vector<double>& V) {
+// recorded and applied to V afterwards, a block of rows at a time.  The result
+// does not depend on `team_max`, the most threads that meet at barriers.
+void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std::vector<double>& V, int team_max) {
   std::vector<double> Vt((size_t)n * n, 0.0);  // V transposed
   for (int i = 0; i < n; ++i) Vt[(size_t)i * n + i] = 1.0;
   std::vector<double> pv(n);
@@ -293,8 +302,7 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
       barrier();
     }
   };
-  const int team = n < kTeamMin ? 1 : std::max(1, std::min(std::min(16, n / kTeamCols),
-                                                           (int)std::thread::hardware_concurrency()));
+  const int team = n < kTeamMin ? 1 : std::max(1, std::min(team_max, n / kTeamCols));
   if (team == 1) {
     reflect(0, 1, []() {});
   } else {
@@ -491,10 +499,10 @@ igafd_status build_direction(int p, int q, int nknots, const double* knots, Dir1
   }
   d.U.clear();
   d.lam.clear();
-  return eig ? eigen_direction(out) : IGAFD_OK;
+  return eig ? eigen_direction(out, eigen_threads(1)) : IGAFD_OK;
 }
 
-igafd_status eigen_direction(Dir1D* out) {
+igafd_status eigen_direction(Dir1D* out, int team_max) {
   Dir1D& d = *out;
   const int n = d.n;
   // generalised eigendecomposition K U = M U D, U^T M U = I
@@ -517,7 +525,7 @@ igafd_status eigen_direction(Dir1D* out) {
       S[(size_t)i * n + j] = S[(size_t)j * n + i] = s;
     }
   std::vector<double> Ut;
-  symmetric_eig(S, n, d.lam, Ut);
+  symmetric_eig(S, n, d.lam, Ut, team_max);
   // U = L^-T Ut: backward substitution on whole rows, L^T upper with band bw
   d.U = Ut;
   for (int i = n - 1; i >= 0; --i) {

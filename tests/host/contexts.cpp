@@ -1,8 +1,14 @@
 // Contexts on the host runtime of hip_double.h.  The argument names a check;
 // prints "OK" and returns 0 when it holds.
+#include <sys/syscall.h>
+#include <unistd.h>
+
+#include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "hip_double.h"
@@ -15,6 +21,18 @@
       return 1;                                              \
     }                                                        \
   } while (0)
+
+namespace {
+std::atomic<int> yielded{0};
+}
+
+// counts the threads that have waited at a barrier long enough to yield
+extern "C" int sched_yield(void) noexcept {
+  static thread_local bool counted = false;
+  if (!counted) yielded += 1;
+  counted = true;
+  return (int)syscall(SYS_sched_yield);
+}
 
 namespace {
 
@@ -88,6 +106,27 @@ int destroyed_stream() {
   hip_double::device_lost = true;
   igafd_destroy(c);
   CHECK(hip_double::bytes_on(0) == 0);
+  return 0;
+}
+
+// Three different directions of 600 unknowns and more: the threads that wait at
+// the barriers of their decompositions, which run at once, stay within one budget.
+int eigen_budget() {
+  std::vector<double> k[3];
+  igafd_problem pr{};
+  pr.dim = 3;
+  pr.degree = 2;
+  for (int l = 0; l < 3; ++l) {
+    k[l] = knots(600 + l, 2);
+    pr.nknots[l] = (int)k[l].size();
+    pr.knots[l] = k[l].data();
+  }
+  igafd_ctx* c = nullptr;
+  CHECK(igafd_setup_precond(&pr, nullptr, &c) == IGAFD_OK);
+  igafd_destroy(c);
+  const int budget = std::max(3, std::min(16, (int)std::thread::hardware_concurrency()));
+  std::printf("%d threads at barriers, budget %d\n", yielded.load(), budget);
+  CHECK(yielded <= budget);
   return 0;
 }
 
@@ -199,6 +238,7 @@ int main(int argc, char** argv) {
   int bad = 1;
   if (what == "destroy_waits") bad = destroy_waits();
   if (what == "destroyed_stream") bad = destroyed_stream();
+  if (what == "eigen_budget") bad = eigen_budget();
   if (what == "cache_fit") bad = cache_fit();
   if (what == "cache_bound_and_age") bad = cache_bound_and_age();
   if (what == "cache_failed_allocation") bad = cache_failed_allocation();

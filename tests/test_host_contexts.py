@@ -46,3 +46,7 @@ def test_release_is_bound():
     import paper_1602_01636_amd as api
     assert api.igafd_release_cached() >= 0
     assert api.igafd_release_cached() == 0
+
+
+def test_decompositions_share_their_threads(contexts):
+    _check(contexts, "eigen_budget")
