@@ -18,9 +18,10 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <memory>
 #include <mutex>
-#include <system_error>
+#include <new>
 #include <thread>
 #include <unordered_map>
 
@@ -34,6 +35,22 @@ thread_local std::string g_err;
 }
 
 void set_error(const std::string& msg) { g_err = msg; }
+
+namespace {
+// the body of a call that allocates host memory: none leaves the C interface as an exception
+template <class F>
+igafd_status guarded(const F& body) {
+  try {
+    return body();
+  } catch (const std::exception&) {
+    try {
+      set_error("out of host memory");
+    } catch (const std::exception&) {
+    }
+    return IGAFD_ERR_ALLOC;
+  }
+}
+}  // namespace
 
 // Device blocks of 1 MiB or more, kept for the next context when one is
 // released.  Returning gigabytes to the driver and taking them again costs a
@@ -60,6 +77,15 @@ std::mutex& g_block_mutex = *new std::mutex;
 std::vector<Block>& g_cached = *new std::vector<Block>;                              // oldest first
 std::unordered_map<void*, Block>& g_blocks = *new std::unordered_map<void*, Block>;  // in use
 long long g_block_clock = 0;
+
+bool record_block(const Block& b) {  // under the mutex
+  try {
+    g_blocks[b.p] = b;
+  } catch (const std::bad_alloc&) {
+    return false;
+  }
+  return true;
+}
 
 void trim_blocks(int device, size_t keep, long long oldest) {  // under the mutex
   size_t held = 0;
@@ -120,11 +146,9 @@ igafd_status block_alloc(void** p, size_t bytes) {
           (best == g_cached.size() || b.bytes < g_cached[best].bytes))
         best = k;
     }
-    if (best < g_cached.size()) {
-      const Block b = g_cached[best];
+    if (best < g_cached.size() && record_block(g_cached[best])) {
+      *p = g_cached[best].p;
       g_cached.erase(g_cached.begin() + (long)best);
-      g_blocks[b.p] = b;
-      *p = b.p;
     }
     trim_blocks(device, kCacheBytes, g_block_clock - kCacheAge);
     if (*p) return IGAFD_OK;
@@ -138,7 +162,7 @@ igafd_status block_alloc(void** p, size_t bytes) {
   }
   if (bytes >= kCacheMin) {
     std::lock_guard<std::mutex> lock(g_block_mutex);
-    g_blocks[*p] = Block{*p, bytes, device, 0};
+    (void)record_block(Block{*p, bytes, device, 0});  // one without a record is not kept later
   }
   return IGAFD_OK;
 }
@@ -172,7 +196,12 @@ void block_free(void* p, bool idle) {
         return;
       }
       b.stamp = g_block_clock;
-      g_cached.push_back(b);
+      try {
+        g_cached.push_back(b);
+      } catch (const std::bad_alloc&) {
+        (void)hipFree(p);
+        return;
+      }
       trim_blocks(b.device, kCacheBytes, g_block_clock - kCacheAge);
       return;
     }
@@ -532,12 +561,19 @@ igafd_status eigen_all(const std::vector<Dir1D*>& dirs) {
   int distinct = 0;
   for (size_t i = 0; i < dirs.size(); ++i) distinct += same[i] == (int)i;
   const int team_max = eigen_threads(distinct);
-  auto run = [&](size_t i) { st[i] = eigen_direction(dirs[i], team_max); };
+  auto run = [&](size_t i) {  // on a thread of its own: nothing may leave it
+    try {
+      st[i] = eigen_direction(dirs[i], team_max);
+    } catch (const std::exception&) {
+      st[i] = IGAFD_ERR_ALLOC;
+    }
+  };
+  th.reserve(dirs.size());
   for (size_t i = 1; i < dirs.size(); ++i) {
     if (same[i] != (int)i) continue;
     try {
       th.emplace_back(run, i);
-    } catch (const std::system_error&) {  // no thread to be had
+    } catch (const std::exception&) {  // no thread to be had
       run(i);
     }
   }
@@ -545,7 +581,7 @@ igafd_status eigen_all(const std::vector<Dir1D*>& dirs) {
   for (std::thread& t : th) t.join();
   for (size_t i = 0; i < dirs.size(); ++i) {
     if (st[i] != IGAFD_OK) {
-      set_error("Cholesky of the 1D mass matrix failed");
+      set_error(st[i] == IGAFD_ERR_ALLOC ? "out of host memory" : "Cholesky of the 1D mass matrix failed");
       return st[i];
     }
     if (same[i] != (int)i) {
@@ -1848,69 +1884,8 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
   *out = c.release();
   return IGAFD_OK;
 }
-}  // namespace
-}  // namespace igafd
 
-extern "C" {
-
-const char* igafd_last_error(void) { return g_err.c_str(); }
-
-igafd_status igafd_univariate(int degree, int nknots, const double* knots, int quad, double* M, double* K, double* U,
-                              double* lam, int* n_out) {
-  Dir1D d;
-  const int q = quad > 0 ? quad : degree + 1;
-  igafd_status s = build_direction(degree, q, nknots, knots, &d);
-  if (s != IGAFD_OK) return s;
-  if (n_out) *n_out = d.n;
-  if (M) std::memcpy(M, d.M.data(), sizeof(double) * d.M.size());
-  if (K) std::memcpy(K, d.K.data(), sizeof(double) * d.K.size());
-  if (U) std::memcpy(U, d.U.data(), sizeof(double) * d.U.size());
-  if (lam) std::memcpy(lam, d.lam.data(), sizeof(double) * d.lam.size());
-  return IGAFD_OK;
-}
-
-long long igafd_release_cached(void) {
-  std::lock_guard<std::mutex> lock(g_block_mutex);
-  long long bytes = 0;
-  for (const Block& b : g_cached) {
-    (void)hipFree(b.p);
-    bytes += (long long)b.bytes;
-  }
-  g_cached.clear();
-  return bytes;
-}
-
-void igafd_destroy(igafd_ctx* c) {
-  if (!c) return;
-  const bool idle = wait_stream(c->stream, c->device);  // its blocks may go to another context and stream
-  for (int k = 0; k < 2; ++k) igafd_destroy(c->sub[k]);
-  adi_free(c);
-  for (int l = 0; l < 3; ++l) free_dir(&c->ddir[l]);
-  for (double* b : {c->band, c->scratch, c->pv_pad, c->xpad, c->scaling}) block_free(b, idle);
-  block_free(c->feat, idle);
-  free_dev(c->ext);
-  free_dev(c->partial);
-  free_dev(c->state);
-  free_dev(c->dflag);
-  if (c->hstate) (void)hipHostFree(c->hstate);
-  if (c->ev0) (void)hipEventDestroy(c->ev0);
-  if (c->ev1) (void)hipEventDestroy(c->ev1);
-  free_dev(c->hist);
-  free_dev(c->modes);
-  for (hipEvent_t e : c->tev) (void)hipEventDestroy(e);
-  delete c;
-}
-
-
-igafd_status igafd_setup(const igafd_problem* pr, void* stream, igafd_ctx** out) {
-  return setup_impl(pr, stream, out, true);
-}
-
-igafd_status igafd_setup_precond(const igafd_problem* pr, void* stream, igafd_ctx** out) {
-  return setup_impl(pr, stream, out, true, false);
-}
-
-igafd_status igafd_lshape_setup(int degree, int nknots, const double* knots, void* stream, igafd_ctx** out) {
+igafd_status lshape_setup_impl(int degree, int nknots, const double* knots, void* stream, igafd_ctx** out) {
   const auto t_start = std::chrono::steady_clock::now();
   if (!knots || !out) {
     set_error("null argument");
@@ -1959,6 +1934,73 @@ igafd_status igafd_lshape_setup(int degree, int nknots, const double* knots, voi
   *out = c.release();
   return IGAFD_OK;
 }
+}  // namespace
+}  // namespace igafd
+
+extern "C" {
+
+const char* igafd_last_error(void) { return g_err.c_str(); }
+
+igafd_status igafd_univariate(int degree, int nknots, const double* knots, int quad, double* M, double* K, double* U,
+                              double* lam, int* n_out) {
+  return guarded([&]() -> igafd_status {
+    Dir1D d;
+    const int q = quad > 0 ? quad : degree + 1;
+    igafd_status s = build_direction(degree, q, nknots, knots, &d);
+    if (s != IGAFD_OK) return s;
+    if (n_out) *n_out = d.n;
+    if (M) std::memcpy(M, d.M.data(), sizeof(double) * d.M.size());
+    if (K) std::memcpy(K, d.K.data(), sizeof(double) * d.K.size());
+    if (U) std::memcpy(U, d.U.data(), sizeof(double) * d.U.size());
+    if (lam) std::memcpy(lam, d.lam.data(), sizeof(double) * d.lam.size());
+    return IGAFD_OK;
+  });
+}
+
+long long igafd_release_cached(void) {
+  std::lock_guard<std::mutex> lock(g_block_mutex);
+  long long bytes = 0;
+  for (const Block& b : g_cached) {
+    (void)hipFree(b.p);
+    bytes += (long long)b.bytes;
+  }
+  g_cached.clear();
+  return bytes;
+}
+
+void igafd_destroy(igafd_ctx* c) {
+  if (!c) return;
+  const bool idle = wait_stream(c->stream, c->device);  // its blocks may go to another context and stream
+  for (int k = 0; k < 2; ++k) igafd_destroy(c->sub[k]);
+  adi_free(c);
+  for (int l = 0; l < 3; ++l) free_dir(&c->ddir[l]);
+  for (double* b : {c->band, c->scratch, c->pv_pad, c->xpad, c->scaling}) block_free(b, idle);
+  block_free(c->feat, idle);
+  free_dev(c->ext);
+  free_dev(c->partial);
+  free_dev(c->state);
+  free_dev(c->dflag);
+  if (c->hstate) (void)hipHostFree(c->hstate);
+  if (c->ev0) (void)hipEventDestroy(c->ev0);
+  if (c->ev1) (void)hipEventDestroy(c->ev1);
+  free_dev(c->hist);
+  free_dev(c->modes);
+  for (hipEvent_t e : c->tev) (void)hipEventDestroy(e);
+  delete c;
+}
+
+
+igafd_status igafd_setup(const igafd_problem* pr, void* stream, igafd_ctx** out) {
+  return guarded([&]() { return setup_impl(pr, stream, out, true); });
+}
+
+igafd_status igafd_setup_precond(const igafd_problem* pr, void* stream, igafd_ctx** out) {
+  return guarded([&]() { return setup_impl(pr, stream, out, true, false); });
+}
+
+igafd_status igafd_lshape_setup(int degree, int nknots, const double* knots, void* stream, igafd_ctx** out) {
+  return guarded([&]() { return lshape_setup_impl(degree, nknots, knots, stream, out); });
+}
 
 }  // extern "C"
 
@@ -1991,11 +2033,11 @@ igafd_status set_adi_impl(igafd_ctx* c, double eps, int rule, int* J, double* rh
 extern "C" {
 
 igafd_status igafd_set_adi(igafd_ctx* c, double eps, int* J, double* rho) {
-  return set_adi_impl(c, eps, kAdiGeometric, J, rho);
+  return guarded([&]() { return set_adi_impl(c, eps, kAdiGeometric, J, rho); });
 }
 
 igafd_status igafd_set_adi_greedy(igafd_ctx* c, double eps, int* J, double* rho) {
-  return set_adi_impl(c, eps, kAdiGreedy, J, rho);
+  return guarded([&]() { return set_adi_impl(c, eps, kAdiGreedy, J, rho); });
 }
 
 igafd_status igafd_get_adi(const igafd_ctx* c, int* J, int* J0, double* rho, double* omegas, int capacity) {

@@ -10,7 +10,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
-#include <system_error>
+#include <exception>
 #include <thread>
 #include <vector>
 
@@ -103,19 +103,19 @@ void span_basis(const double* t, int p, int k, double x, double* N, double* dN) 
   }
 }
 
-// Runs fn(lo, hi) on contiguous chunks of [0, n) on up to 16 host threads
-// (serially when n < 2 * min_chunk).
+// Runs fn(t, lo, hi) on `chunks` contiguous chunks t of [0, n), a host thread each;
+// chunks whose thread cannot be started run on the caller's.  fn must not throw.
 template <class F>
-void parallel_rows(int n, int min_chunk, const F& fn) {
-  const int chunks = std::min(eigen_threads(1), n / std::max(1, min_chunk));
-  if (chunks <= 1) {
-    fn(0, n);
-    return;
-  }
+void parallel_rows(int n, int chunks, const F& fn) {
+  auto chunk = [&](int t) { fn(t, (int)((long long)n * t / chunks), (int)((long long)n * (t + 1) / chunks)); };
   std::vector<std::thread> th;
-  th.reserve(chunks);
-  for (int t = 0; t < chunks; ++t)
-    th.emplace_back(fn, (int)((long long)n * t / chunks), (int)((long long)n * (t + 1) / chunks));
+  int t = 1;
+  try {
+    for (th.reserve(chunks); t < chunks; ++t) th.emplace_back(chunk, t);
+  } catch (const std::exception&) {  // no thread, or no memory for one
+  }
+  chunk(0);
+  for (; t < chunks; ++t) chunk(t);
   for (auto& x : th) x.join();
 }
 
@@ -256,8 +256,10 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
   // barriers per reflector cost more than they save (n = 515: 35 ms alone; a
   // thread started per product and reflector: 90).
   constexpr int kTeamMin = 600, kTeamCols = 96;
+  const int team = n < kTeamMin ? 1 : std::max(1, std::min(team_max, n / kTeamCols));
+  std::vector<double> mine((size_t)team * 3 * n);  // each thread's v, w, t: threads allocate nothing
   auto reflect = [&](int t, int T, auto&& barrier) {
-    std::vector<double> v(n), w(n), tv(n);
+    double *v = &mine[(size_t)t * 3 * n], *w = v + n, *tv = w + n;
     auto share = [&](int m, int* lo, int* hi) {
       *lo = (int)((long long)m * t / T);
       *hi = (int)((long long)m * (t + 1) / T);
@@ -288,7 +290,7 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
       for (int i = 0; i < m; ++i) cvp += v[i] * pv[i];
       for (int i = 0; i < m; ++i) w[i] = pv[i] - cvp * v[i];
       for (int i = lo; i < hi; ++i)
-        op.rank2(&S[(size_t)(k + 1 + i) * n + k + 1], 2.0 * v[i], w.data(), 2.0 * w[i], v.data(), m);
+        op.rank2(&S[(size_t)(k + 1 + i) * n + k + 1], 2.0 * v[i], w, 2.0 * w[i], v, m);
       if (t == 0) {  // column and row k of S are read by nobody before the barrier
         S[(size_t)(k + 1) * n + k] = alpha;
         for (int i = 1; i < m; ++i) S[(size_t)(k + 1 + i) * n + k] = 0.0;
@@ -302,7 +304,6 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
       barrier();
     }
   };
-  const int team = n < kTeamMin ? 1 : std::max(1, std::min(team_max, n / kTeamCols));
   if (team == 1) {
     reflect(0, 1, []() {});
   } else {
@@ -320,12 +321,13 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
     std::vector<std::thread> th;
     std::atomic<bool> go{false};
     try {
+      th.reserve(team);
       for (int t = 1; t < team; ++t)
         th.emplace_back([&, t]() {
           while (!go.load(std::memory_order_acquire)) std::this_thread::yield();
           reflect(t, size.load(std::memory_order_relaxed), barrier);
         });
-    } catch (const std::system_error&) {  // fewer threads than asked for
+    } catch (const std::exception&) {  // fewer threads than asked for
     }
     size.store((int)th.size() + 1, std::memory_order_relaxed);
     go.store(true, std::memory_order_release);
@@ -381,13 +383,15 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
   V.assign((size_t)n * n, 0.0);
   constexpr int B = kRotRows;
   const size_t nrot = rk.size();
-  parallel_rows((n + B - 1) / B, n < 256 ? n : 1, [&](int blo, int bhi) {
-    std::vector<double> T((size_t)n * B);
+  const int blocks = (n + B - 1) / B, chunks = n < 256 ? 1 : std::min(eigen_threads(1), blocks);
+  std::vector<double> runs((size_t)chunks * n * B);
+  parallel_rows(blocks, chunks, [&](int t, int blo, int bhi) {
+    double* T = &runs[(size_t)t * n * B];
     for (int blk = blo; blk < bhi; ++blk) {
       const int r0 = blk * B, nb = std::min(B, n - r0);
       for (int k = 0; k < n; ++k)
         for (int j = 0; j < nb; ++j) T[(size_t)k * B + j] = Vt[(size_t)k * n + r0 + j];
-      op.rotate(T.data(), rk.data(), rc.data(), rs.data(), nrot);
+      op.rotate(T, rk.data(), rc.data(), rs.data(), nrot);
       for (int j = 0; j < nb; ++j)
         for (int k = 0; k < n; ++k) V[(size_t)(r0 + j) * n + k] = T[(size_t)k * B + j];
     }

@@ -6,7 +6,9 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <new>
 #include <string>
 #include <thread>
 #include <vector>
@@ -25,6 +27,24 @@
 namespace {
 std::atomic<int> yielded{0};
 }
+
+// Host allocations: while `fail_at` is not negative, the allocation of that
+// number (counted over all threads) fails.
+namespace {
+std::atomic<long long> fail_at{-1}, allocations{0};
+
+void* host_alloc(size_t n) {
+  if (fail_at >= 0 && !hip_double::inside && allocations++ == fail_at) return nullptr;
+  return std::malloc(n ? n : 1);
+}
+}  // namespace
+void* operator new(size_t n) {
+  if (void* p = host_alloc(n)) return p;
+  throw std::bad_alloc();
+}
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return host_alloc(n); }
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 // counts the threads that have waited at a barrier long enough to yield
 extern "C" int sched_yield(void) noexcept {
@@ -127,6 +147,57 @@ int eigen_budget() {
   const int budget = std::max(3, std::min(16, (int)std::thread::hardware_concurrency()));
   std::printf("%d threads at barriers, budget %d\n", yielded.load(), budget);
   CHECK(yielded <= budget);
+  return 0;
+}
+
+// Each host allocation of a call in turn fails: the call reports it, leaves no
+// device memory behind, and the next call works.
+template <class F>
+int each_allocation_fails(const F& call, long long stride) {
+  for (long long k = 0;; k += stride) {
+    igafd_ctx* c = nullptr;
+    allocations = 0;
+    fail_at = k;
+    const igafd_status st = call(&c);
+    const bool hit = allocations > k;
+    fail_at = -1;
+    CHECK(st == IGAFD_OK || st == IGAFD_ERR_ALLOC);
+    CHECK(hit || st == IGAFD_OK);
+    CHECK((st == IGAFD_OK) == (c != nullptr));
+    if (st == IGAFD_ERR_ALLOC) CHECK(std::string(igafd_last_error()) == "out of host memory");
+    igafd_destroy(c);
+    igafd_release_cached();
+    CHECK(hip_double::live.empty());
+    if (!hit) {
+      std::printf("%lld allocations\n", allocations.load());
+      return 0;
+    }
+  }
+}
+
+int host_memory() {
+  std::vector<double> k[3];
+  igafd_problem pr{};
+  pr.degree = 2;
+  auto sizes = [&](std::vector<int> E) {
+    pr.dim = (int)E.size();
+    for (int l = 0; l < pr.dim; ++l) {
+      k[l] = knots(E[l], 2);
+      pr.nknots[l] = (int)k[l].size();
+      pr.knots[l] = k[l].data();
+    }
+  };
+  sizes({24, 25, 26});
+  pr.want_features = 1;
+  if (each_allocation_fails([&](igafd_ctx** c) { return igafd_setup(&pr, nullptr, c); }, 1)) return 1;
+  sizes({40, 300, 20});  // its rotations are applied by several threads
+  if (each_allocation_fails([&](igafd_ctx** c) { return igafd_setup_precond(&pr, nullptr, c); }, 5)) return 1;
+  sizes({601, 600});     // thread teams
+  if (each_allocation_fails([&](igafd_ctx** c) { return igafd_setup_precond(&pr, nullptr, c); }, 7)) return 1;
+  sizes({20, 21});
+  if (each_allocation_fails(
+          [&](igafd_ctx** c) { return igafd_lshape_setup(2, pr.nknots[0], pr.knots[0], nullptr, c); }, 1))
+    return 1;
   return 0;
 }
 
@@ -239,6 +310,7 @@ int main(int argc, char** argv) {
   if (what == "destroy_waits") bad = destroy_waits();
   if (what == "destroyed_stream") bad = destroyed_stream();
   if (what == "eigen_budget") bad = eigen_budget();
+  if (what == "host_memory") bad = host_memory();
   if (what == "cache_fit") bad = cache_fit();
   if (what == "cache_bound_and_age") bad = cache_bound_and_age();
   if (what == "cache_failed_allocation") bad = cache_failed_allocation();

@@ -34,6 +34,17 @@ struct Attr {
 inline const hipStream_t kWhole = (hipStream_t)-1;
 
 inline std::recursive_mutex mu;
+inline thread_local int inside = 0;    // this thread is in the runtime: its allocations are not the library's
+struct Locked {
+  Locked() {
+    mu.lock();
+    inside += 1;
+  }
+  ~Locked() {
+    inside -= 1;
+    mu.unlock();
+  }
+};
 inline std::map<void*, Alloc> live;    // device allocations
 inline size_t used[2] = {0, 0};        // their bytes per device
 inline size_t capacity = (size_t)288 << 30;
@@ -61,11 +72,11 @@ inline size_t room_from(const void* p) {  // bytes from p to the end of its allo
 
 // live device bytes of a device
 inline size_t bytes_on(int d) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   return used[d];
 }
 inline void forget() {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   syncs.clear();
   attrs.clear();
   mallocs = frees = 0;
@@ -98,7 +109,7 @@ hipError_t hipGetLastError(void) {
 }
 
 hipError_t hipMalloc(void** p, size_t bytes) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   *p = nullptr;
   if (used[device] + bytes > capacity) return done(hipErrorOutOfMemory);
   void* m = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
@@ -110,7 +121,7 @@ hipError_t hipMalloc(void** p, size_t bytes) {
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   if (!p) return hipSuccess;
   const auto it = live.find(p);
   if (it == live.end()) return done(hipErrorInvalidValue);
@@ -131,7 +142,7 @@ hipError_t hipHostFree(void* p) {
 
 // ranges outside the allocation they start in are reported as errors
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   for (const void* p : {(const void*)d, s}) {
     const size_t room = room_from(p);
     if (room && n > room) return done(hipErrorInvalidValue);
@@ -143,25 +154,25 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hip
   return hipMemcpy(d, s, n, k);
 }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   if (n > room_from(d)) return done(hipErrorInvalidValue);
   if (n <= kTouch) std::memset(d, v, n);
   return hipSuccess;
 }
 hipError_t hipMemset2DAsync(void* d, size_t pitch, int, size_t w, size_t h, hipStream_t) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   if (h > 0 && (h - 1) * pitch + w > room_from(d)) return done(hipErrorInvalidValue);
   return hipSuccess;
 }
 
 hipError_t hipStreamSynchronize(hipStream_t s) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   if (dead && s == dead) return done(hipErrorContextIsDestroyed);
   syncs.push_back(Sync{device, s});
   return hipSuccess;
 }
 hipError_t hipDeviceSynchronize(void) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   if (device_lost) return done(hipErrorLaunchFailure);
   syncs.push_back(Sync{device, kWhole});
   return hipSuccess;
@@ -191,7 +202,7 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
   return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void* fn, hipFuncAttribute a, int v) {
-  std::lock_guard<std::recursive_mutex> lock(mu);
+  Locked lock;
   if (a == hipFuncAttributeMaxDynamicSharedMemorySize) attrs.push_back(Attr{fn, v});
   return hipSuccess;
 }

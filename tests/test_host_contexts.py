@@ -50,3 +50,7 @@ def test_release_is_bound():
 
 def test_decompositions_share_their_threads(contexts):
     _check(contexts, "eigen_budget")
+
+
+def test_out_of_host_memory_is_a_status(contexts):
+    _check(contexts, "host_memory")
