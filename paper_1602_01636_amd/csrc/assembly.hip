@@ -1321,7 +1321,7 @@ int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 constexpr long long kAsmWorkMax = 2LL << 30;  // bytes of the direction-3 contraction kept at a time
 constexpr int kAsmBlocks = 2048;              // blocks that fill the chip (256 CUs, several blocks each)
 
-size_t mode_lds(const Modes& md) { return sizeof(double) * 3 * (size_t)md.K * kCol; }
+size_t mode_lds(int K) { return sizeof(double) * 3 * (size_t)K * kCol; }
 
 // functions i3 per thread of the column kernels over `count` of them: long
 // runs repeat less of the evaluation, short ones fill the chip
@@ -1371,13 +1371,17 @@ igafd_status launch_across(igafd_ctx* c, AsmWork* work) {
   IGAFD_HIP_CHECK(
       hipMemset2DAsync(c->band + tail, pitch, 0, sizeof(double) * (size_t)(c->Ns - tail), c->H, c->stream));
   const Modes md = modes_of(c);
-  const size_t col_lds = mode_lds(md), lds3 = col_lds + sizeof(double) * 24 * kCol;
+  const size_t col_lds = mode_lds(md.K), lds3 = col_lds + sizeof(double) * 24 * kCol;
+  // the limit of the function for any problem, not for this one's modes: another
+  // thread's setup of the same degree may be between its setting and its launch
+  constexpr int lds3_max = (int)(sizeof(double) * (3 * kMaxModes + 24) * kCol);
+  static_assert(kMaxModes % kModePad == 0, "padded modes beyond kMaxModes");
   const int colb = cdiv(nq12, kCol);
   const size_t lds = sizeof(double) * (4 * W * R::QS + 2 * R::ELEMS * R::TS);
   IGAFD_HIP_CHECK(
       hipFuncSetAttribute((const void*)k_contract12<P>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   IGAFD_HIP_CHECK(
-      hipFuncSetAttribute((const void*)k_contract3<P>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds3));
+      hipFuncSetAttribute((const void*)k_contract3<P>, hipFuncAttributeMaxDynamicSharedMemorySize, lds3_max));
   const int runs1 = R::runs(c->n[0]), len1 = R::len(c->n[0]);
   for (int base = 0; base < n3; base += run) {
     const int end = std::min(n3, base + run);
@@ -1426,7 +1430,7 @@ igafd_status load_across(igafd_ctx* c, RhsDesc rhs, double* b) {
     const int end = std::min(n3, base + run);
     const int len = column_run(end - base, colb);
     hipLaunchKernelGGL((k_moment3<P, 1>), dim3((unsigned)colb, (unsigned)cdiv(end - base, len)), dim3(kCol),
-                       mode_lds(md), c->stream, T, c->geom, md, rhs, nq1, nq2, (cidx_t*)T.at[2], (ctab_t*)T.qx[2],
+                       mode_lds(md.K), c->stream, T, c->geom, md, rhs, nq1, nq2, (cidx_t*)T.at[2], (ctab_t*)T.qx[2],
                        (ctab_t*)T.qw[2], (ctab_t*)T.val[2], (ctab_t*)md.d3, base, end, len, c->scratch);
     const igafd_status st = moments21<P, 1>(c, T, c->scratch, c->scratch + (end - base) * nq12, base, end, b);
     if (st != IGAFD_OK) return st;

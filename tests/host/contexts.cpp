@@ -201,6 +201,38 @@ int host_memory() {
   return 0;
 }
 
+// The dynamic LDS a function may use is the same for every problem: set to what
+// one problem needs, it could be lowered by one thread's setup between the
+// setting and the launch of another's.
+int lds_limits() {
+  const std::vector<double> k = knots(12, 3);
+  hip_double::forget();
+  for (int modes : {16, 4, 1}) {
+    std::vector<double> g = {0.01, (double)modes};
+    for (int i = 0; i < 3 * modes; ++i) g.push_back(0.1);
+    for (int i = 0; i < 3 * modes; ++i) g.push_back(1.0 + i % 2);
+    igafd_problem pr{};
+    pr.dim = 3;
+    pr.degree = 3;
+    for (int l = 0; l < 3; ++l) {
+      pr.nknots[l] = (int)k.size();
+      pr.knots[l] = k.data();
+    }
+    pr.geom_kind = IGAFD_GEOM_WARPED;
+    pr.geom_params = g.data();
+    pr.n_geom_params = (int)g.size();
+    pr.want_features = 1;
+    igafd_ctx* c = nullptr;
+    CHECK(igafd_setup(&pr, nullptr, &c) == IGAFD_OK);
+    igafd_destroy(c);
+  }
+  CHECK(!hip_double::attrs.empty());
+  for (const hip_double::Attr& a : hip_double::attrs)
+    for (const hip_double::Attr& b : hip_double::attrs) CHECK(a.fn != b.fn || a.value == b.value);
+  CHECK(!hip_double::over_limit);
+  return 0;
+}
+
 constexpr size_t kMiB = 1 << 20, kGiB = (size_t)1 << 30;
 
 void* take(size_t bytes) {
@@ -311,6 +343,7 @@ int main(int argc, char** argv) {
   if (what == "destroyed_stream") bad = destroyed_stream();
   if (what == "eigen_budget") bad = eigen_budget();
   if (what == "host_memory") bad = host_memory();
+  if (what == "lds_limits") bad = lds_limits();
   if (what == "cache_fit") bad = cache_fit();
   if (what == "cache_bound_and_age") bad = cache_bound_and_age();
   if (what == "cache_failed_allocation") bad = cache_failed_allocation();

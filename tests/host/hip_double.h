@@ -51,6 +51,7 @@ inline size_t capacity = (size_t)288 << 30;
 inline long long mallocs = 0, frees = 0;
 inline std::vector<Sync> syncs;
 inline std::vector<Attr> attrs;        // hipFuncSetAttribute, dynamic LDS
+inline bool over_limit = false;        // a launch asked for more dynamic LDS than its function's limit
 inline hipStream_t dead = nullptr;     // a stream that was destroyed: waiting for it fails
 inline bool device_lost = false;       // waiting for the device fails too
 inline thread_local int device = 0;
@@ -206,6 +207,13 @@ hipError_t hipFuncSetAttribute(const void* fn, hipFuncAttribute a, int v) {
   if (a == hipFuncAttributeMaxDynamicSharedMemorySize) attrs.push_back(Attr{fn, v});
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void* fn, dim3, dim3, void**, size_t lds, hipStream_t) {
+  Locked lock;
+  size_t limit = 64 * 1024;
+  for (const Attr& a : attrs)
+    if (a.fn == fn) limit = (size_t)a.value;
+  if (lds > limit) over_limit = true;
+  return hipSuccess;
+}
 
 }  // extern "C"

@@ -54,3 +54,7 @@ def test_decompositions_share_their_threads(contexts):
 
 def test_out_of_host_memory_is_a_status(contexts):
     _check(contexts, "host_memory")
+
+
+def test_lds_limits_do_not_depend_on_the_problem(contexts):
+    _check(contexts, "lds_limits")
