@@ -18,6 +18,10 @@
 // 1027^3 in FP32 65-76 us, of the L-shaped domain's 515 x 1030 pairs in split BF16
 // 47-58 us, of 513^4 in FP64 3.35-3.57 ms; without 49-51, 30-33 and 3.0 ms.  Tiles
 // of 32 x 64 and 32 x 32, with more blocks in flight, moved these by -8 to +20 %.)
+// Right operands of fewer columns than a thread loads at once (one to three, or
+// seven) run the same pipeline with their values loaded one by one: applies of
+// 3 x 1000 in FP64 / FP32 / BF16 / split BF16 113 / 75 / 63 / 72 us, slice by slice
+// without one in flight 138 / 118 / 118 / 137 us.
 // FP64 products are bound by the MFMA rate and its 12 % padding to 64 (53 TFLOP/s of
 // the 73 that a large library product reaches here); the 2D ones by the slice's chain
 // of loads, LDS and MFMAs at one or two blocks per CU.
@@ -236,22 +240,27 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   const bool narrow = !BT && N < EB;  // no EB columns to load as vectors
   const int bcl = BT ? bc : bc - (bn - bn0);  // NN: the columns' place (overlapping copies in an edge tile)
 
+  // the slices' registers must not reach memory: every piece is inlined
+#define IGAFD_INLINE_LAMBDA __attribute__((always_inline))
   struct Stage {
     V a[EA], b[EB];
     double s[PRE ? EA : 1];
   };
-  // full slice: runs of consecutive k (A, BT) or n (NN) as vectors, no conditions,
-  // so that waiting for one slice leaves the next one's loads in flight
-  auto load = [&](int k0, Stage& q) {
+  // full slice: runs of consecutive k (A, BT) or n (NN) as vectors (narrow B: value by
+  // value), no conditions, so that waiting for one slice leaves the next one's loads in flight
+  auto load = [&](auto narrow_b, int k0, Stage& q) IGAFD_INLINE_LAMBDA {
     ldv<EA>(arow + k0 + ak, q.a);
     if (PRE) ldv<EA>(srow + k0 + ak, q.s);
-    if (BT)
+    if constexpr (BT)
       ldv<EB>(brow + k0 + bc, q.b);
+    else if constexpr (decltype(narrow_b)::value)
+#pragma unroll
+      for (int j = 0; j < EB; ++j) q.b[j] = (V)brow[(long long)k0 * ldb + (j < N ? j : N - 1)];
     else
       ldv<EB>(brow + (long long)k0 * ldb, q.b);
   };
-  // any slice, value by value: the last one, K % BK deep, and those of narrow B
-  auto load_tail = [&](int k0, Stage& q) {
+  // the last slice, K % BK deep, value by value
+  auto load_tail = [&](int k0, Stage& q) IGAFD_INLINE_LAMBDA {
 #pragma unroll
     for (int j = 0; j < EA; ++j) {
       const int k = k0 + ak + j < K ? k0 + ak + j : K - 1;
@@ -278,7 +287,7 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
     }
   };
   // write the slice to LDS; TAIL: zeros beyond K
-  auto store = [&](auto tail, int buf, int k0, const Stage& q) {
+  auto store = [&](auto tail, int buf, int k0, const Stage& q) IGAFD_INLINE_LAMBDA {
     constexpr bool TAIL = decltype(tail)::value;
     V* as = As + buf * SA;
     V* bs = Bs + buf * SB;
@@ -316,7 +325,7 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
   const bool off = tm0 + wm0 >= M || tn0 + wn0 >= N;  // this wave's part lies outside the matrix
-  auto compute = [&](int buf) {
+  auto compute = [&](int buf) IGAFD_INLINE_LAMBDA {
     if (off) return;
     const V* as = As + buf * SA;
     const V* bs = Bs + buf * SB;
@@ -384,15 +393,15 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   const std::integral_constant<bool, true> kTail;
   Stage q0, q1;
   // step t: load slice t+2 into stage t&1, compute slice t, store slice t+1
-  auto step = [&](int t, Stage& ql, const Stage& qs) {
-    load((t + 2) * BK, ql);
+  auto step = [&](auto narrow_b, int t, Stage& ql, const Stage& qs) IGAFD_INLINE_LAMBDA {
+    load(narrow_b, (t + 2) * BK, ql);
     __builtin_amdgcn_sched_barrier(0);  // issue the loads first
     compute(t & 1);
     store(kFull, (t + 1) & 1, (t + 1) * BK, qs);
     __syncthreads();
   };
   // the last two full slices and the tail; ql, qs as in step
-  auto finish = [&](int t, Stage& ql, const Stage& qs) {  // t = nf - 2
+  auto finish = [&](int t, Stage& ql, const Stage& qs) IGAFD_INLINE_LAMBDA {  // t = nf - 2
     if (tail) load_tail((t + 2) * BK, ql);
     compute(t & 1);
     store(kFull, (t + 1) & 1, (t + 1) * BK, qs);
@@ -404,42 +413,44 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
       compute(t & 1);
     }
   };
-  if (narrow) {
-    for (int t = 0; t * BK < K; ++t) {
-      load_tail(t * BK, q0);
-      __syncthreads();
-      store(kTail, 0, t * BK, q0);
-      __syncthreads();
-      compute(0);
-    }
-  } else if (nf >= 2) {
-    load(0, q0);
-    load(BK, q1);
-    store(kFull, 0, 0, q0);
-    __syncthreads();
-    int t = 0;
-    for (; t + 3 < nf; t += 2) {
-      step(t, q0, q1);
-      step(t + 1, q1, q0);
-    }
-    if (t + 2 < nf) {
-      step(t, q0, q1);
-      finish(t + 1, q1, q0);
-    } else {
-      finish(t, q0, q1);
-    }
-  } else {
-    if (nf == 1) {
-      load(0, q0);
+  auto run = [&](auto narrow_b) IGAFD_INLINE_LAMBDA {
+    if (nf >= 2) {
+      load(narrow_b, 0, q0);
+      load(narrow_b, BK, q1);
       store(kFull, 0, 0, q0);
+      __syncthreads();
+      int t = 0;
+      for (; t + 3 < nf; t += 2) {
+        step(narrow_b, t, q0, q1);
+        step(narrow_b, t + 1, q1, q0);
+      }
+      if (t + 2 < nf) {
+        step(narrow_b, t, q0, q1);
+        finish(t + 1, q1, q0);
+      } else {
+        finish(t, q0, q1);
+      }
+    } else {
+      if (nf == 1) {
+        load(narrow_b, 0, q0);
+        store(kFull, 0, 0, q0);
+      }
+      if (tail) {
+        load_tail(nf * BK, q1);
+        store(kTail, nf, nf * BK, q1);
+      }
+      __syncthreads();
+      if (nf == 1) compute(0);
+      if (tail) compute(nf);
     }
-    if (tail) {
-      load_tail(nf * BK, q1);
-      store(kTail, nf, nf * BK, q1);
-    }
-    __syncthreads();
-    if (nf == 1) compute(0);
-    if (tail) compute(nf);
+  };
+  if constexpr (BT) {
+    run(kFull);
+  } else {
+    if (narrow)
+      run(kTail);
+    else
+      run(kFull);
   }
 
   double dot = 0.0;
