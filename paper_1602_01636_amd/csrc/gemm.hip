@@ -206,6 +206,11 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   constexpr int EA = BM * BK / kBlock, EB = BN * BK / kBlock;  // values per thread per slice
   constexpr int APR = BK / EA;                                 // threads per row of the A slice
   constexpr int BPR = BT ? BK / EB : BN / EB;                  // threads per row of the stored B slice
+  // an edge tile of fewer than EB columns stores the copies of the columns left of
+  // it up to EB - 1 places before its rows: into the padding of the row before (of
+  // the slice before, for the first row), which nobody reads
+  static_assert(EB <= kPad, "copies of columns left of an edge tile must land in the row padding");
+  static_assert(kPad % 4 == 0 && kGap % 4 == 0, "rows of the slices start at whole 16-byte stores");
   extern __shared__ __align__(16) unsigned char gsm[];
   constexpr int SA = k_row(BK, LA), SB = k_row(BK, LB);        // one slice in LDS
   V* As = reinterpret_cast<V*>(gsm);  // [2][BK][LA], rows at k_row
