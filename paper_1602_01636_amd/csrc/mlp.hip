@@ -263,6 +263,7 @@ __global__ __launch_bounds__(64 * wpb(TRAIN)) void k_mlp(const float* __restrict
     im[NPARAM] = tl;
   }
   __syncthreads();
+  static_assert(!TRAIN || WPB == 2, "a block's sum is that of two waves' images");
   float* out = partial + (long long)blockIdx.x * (NPARAM + 1);
   for (int k = threadIdx.x; k <= NPARAM; k += 64 * WPB) out[k] = s_sum[0][k] + s_sum[TRAIN ? WPB - 1 : 0][k];
 }

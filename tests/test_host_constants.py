@@ -31,6 +31,8 @@ def _compiles(tmp_path, source, old=None, new=None):
     # copies of columns left of an edge tile land in the padding of the LDS rows
     ("gemm.hip", "constexpr int kPad = 16;", "constexpr int kPad = 4;"),
     ("gemm.hip", "constexpr int kGap = 16;", "constexpr int kGap = 2;"),
+    # a training block adds the gradient images of its two waves
+    ("mlp.hip", "return train ? 2 : kBlock / 64;", "return train ? 4 : kBlock / 64;"),
 ])
 def test_dependent_constants(tmp_path, source, old, new):
     ok, err = _compiles(tmp_path, source)
