@@ -583,7 +583,7 @@ int lines_per_block(const igafd_ctx* c, int dir, int mode) {
   for (int lt : {32, 16}) {
     const size_t lds = adi_lds<P>(mode, lt, c->n[dir]);
     if (lds > kAdiLds) continue;
-    if (lt == 16 || (adi_lines(c, dir) + lt - 1) / lt <= 256 * (long long)(kAdiLds / lds)) return lt;
+    if (lt == 16 || (adi_lines(c, dir) + lt - 1) / lt <= device_cus() * (long long)(kAdiLds / lds)) return lt;
   }
   return 0;
 }

@@ -42,6 +42,17 @@
 #include "reduce.h"
 
 namespace igafd {
+
+int device_cus() {
+  static const int cus = []() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+      n = 256;
+    return n;
+  }();
+  return cus;
+}
 namespace {
 
 typedef double gd4_t __attribute__((ext_vector_type(4)));
@@ -485,17 +496,6 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
 struct Cfg {
   int tm, tn;
 };
-
-int device_cus() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-      cus = 256;
-  }
-  return cus;
-}
 
 // Tile shape: the one with the least work on the busiest CU, estimated as
 // ceil(tiles / CUs) x tile area (tiles are dealt evenly, all take the same

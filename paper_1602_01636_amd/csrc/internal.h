@@ -34,6 +34,7 @@ hipError_t device_malloc(void** p, size_t bytes);  // hipMalloc; where that fail
 // idle: everything that used the block has finished (else it goes to the driver)
 void block_free(void* p, bool idle = true);
 bool wait_stream(hipStream_t stream, int device);  // false: could not be waited for
+int device_cus();  // compute units of the first device used (gemm.hip)
 // block partials (per sum) a context's reductions may write; sizes its buffer
 int partial_capacity(const igafd_ctx* c);
 

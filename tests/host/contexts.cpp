@@ -233,6 +233,23 @@ int lds_limits() {
   return 0;
 }
 
+// The ADI sub-steps take half the lines per block where 32 would not all be
+// resident at once: by the device's compute units.
+int adi_lines() {
+  hip_double::cus = 32;  // a partition of the card
+  igafd_ctx c;
+  c.dim = 3;
+  c.p = 3;
+  c.n[0] = c.n[1] = c.n[2] = 97;
+  c.N = 97LL * 97 * 97;
+  c.npartial = igafd::partial_capacity(&c);
+  CHECK(igafd::adi_dot_blocks(&c) == (97 * 97 + 15) / 16);
+  c.n[0] = c.n[1] = 20;  // 400 lines: 13 blocks of 32
+  c.N = 400LL * 97;
+  CHECK(igafd::adi_dot_blocks(&c) == 13);
+  return 0;
+}
+
 constexpr size_t kMiB = 1 << 20, kGiB = (size_t)1 << 30;
 
 void* take(size_t bytes) {
@@ -344,6 +361,7 @@ int main(int argc, char** argv) {
   if (what == "eigen_budget") bad = eigen_budget();
   if (what == "host_memory") bad = host_memory();
   if (what == "lds_limits") bad = lds_limits();
+  if (what == "adi_lines") bad = adi_lines();
   if (what == "cache_fit") bad = cache_fit();
   if (what == "cache_bound_and_age") bad = cache_bound_and_age();
   if (what == "cache_failed_allocation") bad = cache_failed_allocation();

@@ -51,6 +51,7 @@ inline size_t capacity = (size_t)288 << 30;
 inline long long mallocs = 0, frees = 0;
 inline std::vector<Sync> syncs;
 inline std::vector<Attr> attrs;        // hipFuncSetAttribute, dynamic LDS
+inline int cus = 256;
 inline bool over_limit = false;        // a launch asked for more dynamic LDS than its function's limit
 inline hipStream_t dead = nullptr;     // a stream that was destroyed: waiting for it fails
 inline bool device_lost = false;       // waiting for the device fails too
@@ -99,7 +100,7 @@ hipError_t hipSetDevice(int d) {
   return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
-  *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 160 * 1024;  // the others asked for are LDS sizes
+  *v = a == hipDeviceAttributeMultiprocessorCount ? cus : 160 * 1024;  // the others asked for are LDS sizes
   return hipSuccess;
 }
 const char* hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }

@@ -58,3 +58,7 @@ def test_out_of_host_memory_is_a_status(contexts):
 
 def test_lds_limits_do_not_depend_on_the_problem(contexts):
     _check(contexts, "lds_limits")
+
+
+def test_adi_lines_by_the_device(contexts):
+    _check(contexts, "adi_lines")
