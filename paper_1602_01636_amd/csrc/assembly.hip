@@ -126,25 +126,26 @@ __host__ __device__ constexpr int sym_index(int a, int b) {
 }
 
 // Per-dof statistics of the learned scaling, one element's share: for the
-// NCH channels ch0..ch0+NCH-1 and every local function a = (a1, a2, a3) of
+// kChan channels and every local function a = (a1, a2, a3) of
 // the element, sum_t B_a(t) v(ch, t) over the element's Gauss points t, where
 // v(ch, t) = w_t G_ch(t) (ch < 6: the entries 11, 22, 33, 12, 13, 23 of
 // G = |det J| J^-1 J^-T), w_t kappa(t) (ch = 6) or w_t (ch = 7), given in
-// vals[ch - ch0][t].  The sum is taken one direction at a time (sum
+// vals[ch][t].  The sum is taken one direction at a time (sum
 // factorisation: t1, then t2, then t3) and added into acc[8 row + ch] for the
 // functions that are dofs; the element's colour class guarantees no other
-// block adds to those rows.  F1 (NCH L Q Q3 doubles) and F2 (NCH L L Q3) are
+// block adds to those rows.  F1 (kChan L Q Q3 doubles) and F2 (kChan L L Q3) are
 // LDS scratch; vals may share F2's storage (it is last read before F2 is
 // written).
-template <int D, int P, int NCH>
-__device__ void feature_sums(int ch0, const double* vals, const double (*sV)[P + 1][P + 1], const int* first,
+constexpr int kChan = 8;
+template <int D, int P>
+__device__ void feature_sums(const double* vals, const double (*sV)[P + 1][P + 1], const int* first,
                              const Tables& T, double* F1, double* F2, double* __restrict__ acc) {
   constexpr int Q = P + 1, L = P + 1;
   constexpr int Q3 = (D == 3) ? Q : 1;
   constexpr int L3 = (D == 3) ? L : 1;
   constexpr int NQ = Q * Q * Q3;
   const int tid = threadIdx.x;
-  for (int idx = tid; idx < NCH * L * Q * Q3; idx += kBlock) {  // F1[c][t2 + Q t3][a1]
+  for (int idx = tid; idx < kChan * L * Q * Q3; idx += kBlock) {  // F1[c][t2 + Q t3][a1]
     const int c = idx / (L * Q * Q3), r = idx % (L * Q * Q3);
     const int a1 = r % L, t23 = r / L;
     double s = 0.0;
@@ -153,7 +154,7 @@ __device__ void feature_sums(int ch0, const double* vals, const double (*sV)[P +
     F1[idx] = s;
   }
   __syncthreads();
-  for (int idx = tid; idx < NCH * L * L * Q3; idx += kBlock) {  // F2[c][t3][a2][a1]
+  for (int idx = tid; idx < kChan * L * L * Q3; idx += kBlock) {  // F2[c][t3][a2][a1]
     const int c = idx / (L * L * Q3), r = idx % (L * L * Q3);
     const int a1 = r % L, a2 = (r / L) % L, t3 = r / (L * L);
     double s = 0.0;
@@ -162,10 +163,9 @@ __device__ void feature_sums(int ch0, const double* vals, const double (*sV)[P +
     F2[idx] = s;
   }
   __syncthreads();
-  // one thread per local function: its NCH channel sums, then one
-  // read-modify-write of the NCH consecutive doubles of its row (a 32- or
-  // 64-byte run, instead of NCH scattered 8-byte accesses from as many waves)
-  static_assert(NCH % 4 == 0, "channel quadruples");
+  // one thread per local function: its kChan channel sums, then one
+  // read-modify-write of the kChan consecutive doubles of its row (a 64-byte run,
+  // instead of kChan scattered 8-byte accesses from as many waves)
   typedef double dpair __attribute__((ext_vector_type(2)));
   constexpr int DOFS = L * L * L3, PER = (DOFS + kBlock - 1) / kBlock;
 #pragma unroll
@@ -175,11 +175,10 @@ __device__ void feature_sums(int ch0, const double* vals, const double (*sV)[P +
     const int a1 = r % L, a2 = (r / L) % L, a3 = r / (L * L);
     const int r1 = first[0] + a1 - 1, r2 = first[1] + a2 - 1, r3 = (D == 3) ? first[2] + a3 - 1 : 0;
     if (r1 < 0 || r1 >= T.n[0] || r2 < 0 || r2 >= T.n[1] || r3 < 0 || r3 >= T.n[2]) continue;
-    dpair* row = reinterpret_cast<dpair*>(acc + 8 * (r1 + (long long)T.n[0] * (r2 + (long long)T.n[1] * r3)) + ch0);
-    // four channels at a time (the registers of eight sums and their old
-    // values would cost the p = 4 assembly a wave per SIMD)
+    dpair* row = reinterpret_cast<dpair*>(acc + 8 * (r1 + (long long)T.n[0] * (r2 + (long long)T.n[1] * r3)));
+    // four channels at a time (fewer registers than eight sums and their old values)
 #pragma unroll
-    for (int h = 0; h < NCH; h += 4) {
+    for (int h = 0; h < kChan; h += 4) {
       const dpair o0 = row[h / 2], o1 = row[h / 2 + 1];
       double sv[4];
 #pragma unroll
@@ -196,8 +195,9 @@ __device__ void feature_sums(int ch0, const double* vals, const double (*sV)[P +
   __syncthreads();
 }
 
-// FEAT = 1: also the per-dof feature sums of the learned scaling into acc
-// (8 doubles per dof), from the same Gauss-point evaluation of the map.
+// FEAT = 1 (2D; 3D contexts with features are assembled across the elements):
+// also the per-dof feature sums of the learned scaling into acc (8 doubles per
+// dof), from the same Gauss-point evaluation of the map.
 template <int D, int P, int FEAT>
 __global__ __launch_bounds__(kBlock, (D == 3 && P <= 4) ? 5 : 1) void k_assemble(Tables T, GeomDesc g, double* __restrict__ band,
                                                      long long Ns, int c1, int c2, int c3, int m1, int m2,
@@ -220,12 +220,10 @@ __global__ __launch_bounds__(kBlock, (D == 3 && P <= 4) ? 5 : 1) void k_assemble
   __shared__ double sG[NAB][L * L][Q];
   __shared__ int sFirst[3];
   // features: kappa and the weight per point, F2 of the contraction (F1 lives in sG)
+  static_assert(!FEAT || D == 2, "features with A by elements in 2D only");
   __shared__ double sKap[FEAT ? NQ : 1], sW[FEAT ? NQ : 1];
-  // feature channels per pass: all eight, or four at a time from p = 5 on
-  // (eight made the LDS of p = 5 allow three blocks per CU instead of four)
-  constexpr int NCH = (P >= 5) ? 4 : 8;
-  __shared__ double sF2[FEAT ? NCH * L * L * Q3 : 1];  // the channel values, then F2
-  static_assert(!FEAT || NAB * L * L * Q >= NCH * L * Q * Q3, "feature scratch F1 must fit in sG");
+  __shared__ double sF2[FEAT ? kChan * L * L * Q3 : 1];  // the channel values, then F2
+  static_assert(!FEAT || NAB * L * L * Q >= kChan * L * Q * Q3, "feature scratch F1 must fit in sG");
   static_assert(!FEAT || L * L * Q3 >= NQ, "channel values must fit in sF2");
 
   int bid = blockIdx.x;
@@ -275,26 +273,23 @@ __global__ __launch_bounds__(kBlock, (D == 3 && P <= 4) ? 5 : 1) void k_assemble
   }
   __syncthreads();
   if (FEAT) {
-    // the channel values at the Gauss points, once each per pass: w G_ab =
-    // C_ab / kappa; the channel order is (11, 22, 33, 12, 13, 23, kappa, 1)
-    for (int ch0 = 0; ch0 < 8; ch0 += NCH) {
-      for (int idx = tid; idx < NCH * NQ; idx += kBlock) {
-        const int ch = ch0 + idx / NQ, t = idx % NQ;
-        constexpr int ia[6] = {0, 1, 2, 0, 0, 1}, ib[6] = {0, 1, 2, 1, 2, 2};
-        double v;
-        if (ch == 6)
-          v = sW[t] * sKap[t];
-        else if (ch == 7)
-          v = sW[t];
-        else if (ia[ch] >= D || ib[ch] >= D)
-          v = 0.0;
-        else
-          v = sC[sym_index<D>(ia[ch], ib[ch])][t] / sKap[t];
-        sF2[idx] = v;
-      }
-      __syncthreads();
-      feature_sums<D, P, NCH>(ch0, sF2, sV, sFirst, T, &sG[0][0][0], sF2, acc);
+    // the channel values at the Gauss points: w G_ab = C_ab / kappa; the channel
+    // order is (11, 22, 33, 12, 13, 23, kappa, 1), those of direction 3 zero
+    for (int idx = tid; idx < kChan * NQ; idx += kBlock) {
+      const int ch = idx / NQ, t = idx % NQ;
+      double v;
+      if (ch == 6)
+        v = sW[t] * sKap[t];
+      else if (ch == 7)
+        v = sW[t];
+      else if (ch == 2 || ch > 3)
+        v = 0.0;
+      else
+        v = sC[ch == 3 ? sym_index<D>(0, 1) : sym_index<D>(ch, ch)][t] / sKap[t];
+      sF2[idx] = v;
     }
+    __syncthreads();
+    feature_sums<D, P>(sF2, sV, sFirst, T, &sG[0][0][0], sF2, acc);
   }
 
   for (int a3 = 0; a3 < L3; ++a3) {
@@ -1136,7 +1131,7 @@ __global__ __launch_bounds__(kBlock) void k_features(Tables T, GeomDesc g, doubl
     sf[7][t] = w;
   }
   __syncthreads();
-  feature_sums<D, P, 8>(0, &sf[0][0], sV, sFirst, T, sF1, sF2, acc);
+  feature_sums<D, P>(&sf[0][0], sV, sFirst, T, sF1, sF2, acc);
 }
 
 // Extreme eigenvalues of a symmetric positive definite 2x2 / 3x3 matrix.
