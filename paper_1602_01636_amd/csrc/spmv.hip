@@ -499,8 +499,11 @@ igafd_status launch_r(igafd_ctx* c, const double* xpad, double* y, double* parti
 
 // Dynamic LDS above 64 KB needs the kernel attribute; set once when a tile
 // shape is selected (never inside a launch sequence that may be captured).
+// The functions' limit is all of a CU's LDS for every problem, never what one
+// problem needs: other contexts' launches may come between.
+constexpr int kLdsMax = 160 * 1024;
 template <int P, int TB>
-igafd_status tile_lds_attr_tb(int ch, int lds) {
+igafd_status tile_lds_attr_tb(int ch) {
   const void* fn = nullptr;
   switch (ch) {
 #define IGAFD_CH(K)                              \
@@ -513,13 +516,13 @@ igafd_status tile_lds_attr_tb(int ch, int lds) {
       set_error("internal: bad tile chunk count");
       return IGAFD_ERR_ARG;
   }
-  IGAFD_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+  IGAFD_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax));
   return IGAFD_OK;
 }
 
 template <int P>
-igafd_status tile_lds_attr(int ch, int lds, int tb) {
-  return tb == 512 ? tile_lds_attr_tb<P, 512>(ch, lds) : tile_lds_attr_tb<P, 256>(ch, lds);
+igafd_status tile_lds_attr(int ch, int tb) {
+  return tb == 512 ? tile_lds_attr_tb<P, 512>(ch) : tile_lds_attr_tb<P, 256>(ch);
 }
 
 template <int P, int CH>
@@ -669,7 +672,7 @@ igafd_status spmv_set_tile(igafd_ctx* c, int b2, int b3, int tb) {
     switch (p) {
 #define IGAFD_TCASE(P)                          \
   case P:                                       \
-    s = tile_lds_attr<P>(ch, (int)lds, tb);     \
+    s = tile_lds_attr<P>(ch, tb);               \
     break;
       IGAFD_TCASE(1) IGAFD_TCASE(2) IGAFD_TCASE(3) IGAFD_TCASE(4) IGAFD_TCASE(5) IGAFD_TCASE(6)
 #undef IGAFD_TCASE
@@ -753,17 +756,17 @@ igafd_status tile_g_launch(const TileJob* jobs, const int* start, int njobs, int
 }
 
 template <int P, int CH, int TB>
-igafd_status tile_g_attr(size_t lds) {
+igafd_status tile_g_attr() {
   IGAFD_HIP_CHECK(hipFuncSetAttribute((const void*)k_spmv_tile_g<P, CH, TB>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMax));
   return IGAFD_OK;
 }
 
 template <int P, int CH>
 igafd_status tile_g_tb(int tb, bool attr, const TileJob* jobs, const int* start, int njobs, int blocks, size_t lds,
                        hipStream_t st) {
-  if (tb == 512) return attr ? tile_g_attr<P, CH, 512>(lds) : tile_g_launch<P, CH, 512>(jobs, start, njobs, blocks, lds, st);
-  return attr ? tile_g_attr<P, CH, 256>(lds) : tile_g_launch<P, CH, 256>(jobs, start, njobs, blocks, lds, st);
+  if (tb == 512) return attr ? tile_g_attr<P, CH, 512>() : tile_g_launch<P, CH, 512>(jobs, start, njobs, blocks, lds, st);
+  return attr ? tile_g_attr<P, CH, 256>() : tile_g_launch<P, CH, 256>(jobs, start, njobs, blocks, lds, st);
 }
 
 // (p, chunk count, threads per block) -> the grouped tile kernel's launch or

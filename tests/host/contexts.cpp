@@ -226,6 +226,11 @@ int lds_limits() {
     CHECK(igafd_setup(&pr, nullptr, &c) == IGAFD_OK);
     igafd_destroy(c);
   }
+  for (int E : {128, 120, 112, 104, 96, 88}) {  // tiled A products of one degree, different tiles
+    igafd_ctx* c = setup(E, 3, nullptr);
+    CHECK(c && igafd_apply_A(c, c->r, c->z) == IGAFD_OK);
+    igafd_destroy(c);
+  }
   CHECK(!hip_double::attrs.empty());
   for (const hip_double::Attr& a : hip_double::attrs)
     for (const hip_double::Attr& b : hip_double::attrs) CHECK(a.fn != b.fn || a.value == b.value);
