@@ -121,17 +121,6 @@ hipError_t device_malloc(void** p, size_t bytes) {
   return e;
 }
 
-// a tile shape whose buffer found no room is tried once more without the cache
-static igafd_status set_tile(igafd_ctx* c, int b2, int b3, int tb) {
-  igafd_status s = spmv_set_tile(c, b2, b3, tb);
-  if (s == IGAFD_ERR_HIP) {
-    (void)hipGetLastError();
-    drop_blocks();
-    s = spmv_set_tile(c, b2, b3, tb);
-  }
-  return s;
-}
-
 igafd_status block_alloc(void** p, size_t bytes) {
   *p = nullptr;
   int device = 0;
@@ -1752,7 +1741,7 @@ igafd_status autotune_impl(igafd_ctx* c, int reps) {
   Cand best_c{c->spmv_rows, c->tile_b2, c->tile_b3, c->tile_tb};
   for (const Cand& k : cands) {
     c->spmv_rows = k.rows;
-    if (set_tile(c, k.b2, k.b3, k.tb) != IGAFD_OK) continue;
+    if (spmv_set_tile(c, k.b2, k.b3, k.tb) != IGAFD_OK) continue;
     bool ok = true;
     const float ms = time_it([&]() { ok = ok && spmv(c, c->pv, c->q, nullptr, nullptr) == IGAFD_OK; });
     // a later candidate must be 1% faster: near-ties keep the earlier one, so
@@ -1763,7 +1752,7 @@ igafd_status autotune_impl(igafd_ctx* c, int reps) {
     }
   }
   c->spmv_rows = best_c.rows;
-  IGAFD_TRY(set_tile(c, best_c.b2, best_c.b3, best_c.tb));
+  IGAFD_TRY(spmv_set_tile(c, best_c.b2, best_c.b3, best_c.tb));
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
   IGAFD_HIP_CHECK(hipGetLastError());
@@ -1872,7 +1861,7 @@ igafd_status setup_impl(const igafd_problem* pr, void* stream, igafd_ctx** out, 
         tb = 512;
       }
     }
-    if ((s = set_tile(c.get(), b2, b3, tb)) != IGAFD_OK) return s;
+    if ((s = spmv_set_tile(c.get(), b2, b3, tb)) != IGAFD_OK) return s;
   }
   // the device assembles A while the host computes the eigendecompositions
   AsmWork work{nullptr, c.get()};
@@ -1974,9 +1963,8 @@ void igafd_destroy(igafd_ctx* c) {
   for (int k = 0; k < 2; ++k) igafd_destroy(c->sub[k]);
   adi_free(c);
   for (int l = 0; l < 3; ++l) free_dir(&c->ddir[l]);
-  for (double* b : {c->band, c->scratch, c->pv_pad, c->xpad, c->scaling}) block_free(b, idle);
+  for (double* b : {c->band, c->ext, c->scratch, c->pv_pad, c->xpad, c->scaling}) block_free(b, idle);
   block_free(c->feat, idle);
-  free_dev(c->ext);
   free_dev(c->partial);
   free_dev(c->state);
   free_dev(c->dflag);

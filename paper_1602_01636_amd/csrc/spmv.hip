@@ -683,10 +683,11 @@ igafd_status spmv_set_tile(igafd_ctx* c, int b2, int b3, int tb) {
     if (s != IGAFD_OK) return s;
   }
   if (need > c->ext_cap) {
-    if (c->ext) IGAFD_HIP_CHECK(hipFree(c->ext));
+    if (c->ext) block_free(c->ext, wait_stream(c->stream, c->device));
     c->ext = nullptr;
     c->ext_cap = 0;
-    IGAFD_HIP_CHECK(hipMalloc((void**)&c->ext, sizeof(double) * (size_t)need));
+    const igafd_status s = block_alloc((void**)&c->ext, sizeof(double) * (size_t)need);
+    if (s != IGAFD_OK) return s;
     c->ext_cap = need;
   }
   c->tile_b2 = b2;

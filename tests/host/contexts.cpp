@@ -291,6 +291,18 @@ int cache_fit() {
   return 0;
 }
 
+// Every large buffer of a second context of the same problem comes from the first one's.
+int cache_holds_all() {
+  igafd_ctx* c = setup(64, 3, nullptr, true);
+  CHECK(c);
+  igafd_destroy(c);
+  hip_double::forget();
+  c = setup(64, 3, nullptr, true);
+  CHECK(c && hip_double::large_mallocs == 0);
+  igafd_destroy(c);
+  return 0;
+}
+
 // At most 8 GiB per device, the oldest given back first; blocks without use
 // for 64 later requests are given back.
 int cache_bound_and_age() {
@@ -368,6 +380,7 @@ int main(int argc, char** argv) {
   if (what == "lds_limits") bad = lds_limits();
   if (what == "adi_lines") bad = adi_lines();
   if (what == "cache_fit") bad = cache_fit();
+  if (what == "cache_holds_all") bad = cache_holds_all();
   if (what == "cache_bound_and_age") bad = cache_bound_and_age();
   if (what == "cache_failed_allocation") bad = cache_failed_allocation();
   if (what == "cache_release") bad = cache_release();

@@ -48,7 +48,7 @@ struct Locked {
 inline std::map<void*, Alloc> live;    // device allocations
 inline size_t used[2] = {0, 0};        // their bytes per device
 inline size_t capacity = (size_t)288 << 30;
-inline long long mallocs = 0, frees = 0;
+inline long long large_mallocs = 0, frees = 0;  // of 1 MiB and more; all
 inline std::vector<Sync> syncs;
 inline std::vector<Attr> attrs;        // hipFuncSetAttribute, dynamic LDS
 inline int cus = 256;
@@ -81,7 +81,7 @@ inline void forget() {
   Locked lock;
   syncs.clear();
   attrs.clear();
-  mallocs = frees = 0;
+  large_mallocs = frees = 0;
 }
 
 }  // namespace hip_double
@@ -118,7 +118,7 @@ hipError_t hipMalloc(void** p, size_t bytes) {
   if (m == MAP_FAILED) return done(hipErrorOutOfMemory);
   live[m] = Alloc{bytes, device};
   used[device] += bytes;
-  mallocs += 1;
+  large_mallocs += bytes >= (1 << 20);
   *p = m;
   return hipSuccess;
 }

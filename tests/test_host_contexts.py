@@ -37,7 +37,7 @@ def test_memory_is_handed_on_after_its_stream(contexts, what):
     _check(contexts, what)
 
 
-@pytest.mark.parametrize("what", ["cache_fit", "cache_bound_and_age", "cache_failed_allocation", "cache_release"])
+@pytest.mark.parametrize("what", ["cache_fit", "cache_holds_all", "cache_bound_and_age", "cache_failed_allocation", "cache_release"])
 def test_block_cache(contexts, what):
     _check(contexts, what)
 
