@@ -103,7 +103,12 @@ typedef struct {
   int quad_per_dir;            /* Gauss points per element and direction: 0 or p+1             */
   int want_features;           /* 1: igafd_setup also sums the per-dof inputs of the learned
                                   scaling (igafd_features) from the Gauss-point values it
-                                  evaluates for A, and keeps them (8N floats)                  */
+                                  evaluates for A, and keeps them (8N floats).  In 3D the flag
+                                  also selects another summation order for A and for
+                                  igafd_load_vector: both agree with those of a context without
+                                  features to rounding, not bit for bit (two solves with plain
+                                  BF16 applies differ by up to about 3e-9 at rtol 1e-8), and the
+                                  setup is faster, at 112^3 with p = 4 by 0.17 s of 0.19      */
 } igafd_problem;
 
 /*

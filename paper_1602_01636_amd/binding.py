@@ -220,7 +220,9 @@ class Context:
 
 def igafd_setup(problem: dict, stream=None, features=False) -> Context:
     """Setup of one problem (host 1D setup + device assembly); features=True
-    also assembles the learned scaling's per-dof inputs."""
+    also assembles the learned scaling's per-dof inputs (in 3D with A and load
+    vectors summed in another order: equal to rounding, not bit for bit, and a
+    faster setup)."""
     return _setup(problem, stream, "igafd_setup", features)
 
 

@@ -22,13 +22,15 @@
 // by one thread, once.  Features and load vectors go the same way.
 // Measured, warped cube with kappa: 112^3, p = 4: 15.1 ms for the band (4.3 GB)
 // against 197 ms by colours (which read, add to and write it); load vector 2.9
-// against 22.6 ms; 16^3, p = 3: 42 us in 2 launches against 1.7 ms in 64.
+// against 22.6 ms; 16^3, p = 3: 0.21 ms in 10 launches against 1.7 ms in 64.
 //
 // Both sums are in a fixed order (bitwise reproducible, no atomics), but not in
-// the same one: the entries differ in their last bits.  Contexts without the
-// features keep the element order because flexible CG with plain BF16 applies
-// turns a last bit of A or b into up to 3e-9 of the solution (the applies round
-// to 8 bits, and the iterates take another path within the same tolerance).
+// the same one: the entries differ in their last bits.  A context's order is a
+// matter of its features alone, whatever precision its solves use: contexts
+// without them keep the element order, so that their results stay what they
+// were bit for bit (flexible CG with plain BF16 applies turns a last bit of A or
+// b into up to 3e-9 of the solution, the iterates taking another path within
+// the same tolerance; the other precisions follow to rounding).
 #include <algorithm>
 
 #include "internal.h"
