@@ -547,12 +547,13 @@ igafd_status eigen_all(const std::vector<Dir1D*>& dirs) {
     for (size_t j = 0; j < i && same[i] == (int)i; ++j)
       if (dirs[j]->p == dirs[i]->p && dirs[j]->q == dirs[i]->q && dirs[j]->knots == dirs[i]->knots) same[i] = (int)j;
   }
-  int distinct = 0;
-  for (size_t i = 0; i < dirs.size(); ++i) distinct += same[i] == (int)i;
-  const int team_max = eigen_threads(distinct);
+  auto work = [&](size_t i) { return std::pow((double)dirs[i]->n, 3); };
+  double all = 0.0;
+  for (size_t i = 0; i < dirs.size(); ++i)
+    if (same[i] == (int)i) all += work(i);
   auto run = [&](size_t i) {  // on a thread of its own: nothing may leave it
     try {
-      st[i] = eigen_direction(dirs[i], team_max);
+      st[i] = eigen_direction(dirs[i], eigen_threads(work(i) / all));
     } catch (const std::exception&) {
       st[i] = IGAFD_ERR_ALLOC;
     }

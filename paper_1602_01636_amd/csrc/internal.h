@@ -75,7 +75,7 @@ igafd_status build_direction(int p, int q, int nknots, const double* knots, Dir1
 
 // U and lam of a direction built without them; team_max: the most threads of its team
 igafd_status eigen_direction(Dir1D* d, int team_max);
-int eigen_threads(int concurrent);  // team_max of each of several decompositions at once
+int eigen_threads(double share);  // team_max of one with this share of the work that runs at once
 
 // Device copies of one direction.
 struct DevDir {

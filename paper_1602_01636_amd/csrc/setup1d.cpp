@@ -19,13 +19,15 @@
 namespace igafd {
 
 // A team's threads spin at two barriers per reflector, so the decompositions
-// that run at once share one budget of 16 team threads (or the CPUs, if fewer).
-// Setups on 16 CPUs with 16 for each and with 16 in all: three directions of
-// n = 620-640 150 and 128 ms, two of 1000 400 and 335 ms, two of 1500-1600 1.1
-// and 1.2 s; one team at a time 260 ms, 515 ms and 1.45 s.
-int eigen_threads(int concurrent) {
+// that run at once share one budget of 16 team threads (or the CPUs, if fewer),
+// by their work: share is one's part of it.  Setups on 16 CPUs with 16 for each
+// and with 16 in all: n = 620-640 in three directions 152 and 129 ms, 700 x 1100
+// 376 and 350 ms, 1000 x 1001 400 and 338 ms, 1500 x 1600 1.07 and 1.2 s (the same
+// threads in equal shares: 700 x 1100 390 ms); one team at a time 260, 440, 510 ms
+// and 1.4 s.
+int eigen_threads(double share) {
   const int all = std::min(16, (int)std::thread::hardware_concurrency());
-  return std::max(1, all / std::max(1, concurrent));
+  return std::max(1, (int)(all * share));
 }
 
 namespace {
@@ -383,7 +385,7 @@ void symmetric_eig(std::vector<double>& S, int n, std::vector<double>& lam, std:
   V.assign((size_t)n * n, 0.0);
   constexpr int B = kRotRows;
   const size_t nrot = rk.size();
-  const int blocks = (n + B - 1) / B, chunks = n < 256 ? 1 : std::min(eigen_threads(1), blocks);
+  const int blocks = (n + B - 1) / B, chunks = n < 256 ? 1 : std::min(eigen_threads(1.0), blocks);
   std::vector<double> runs((size_t)chunks * n * B);
   parallel_rows(blocks, chunks, [&](int t, int blo, int bhi) {
     double* T = &runs[(size_t)t * n * B];
@@ -503,7 +505,7 @@ igafd_status build_direction(int p, int q, int nknots, const double* knots, Dir1
   }
   d.U.clear();
   d.lam.clear();
-  return eig ? eigen_direction(out, eigen_threads(1)) : IGAFD_OK;
+  return eig ? eigen_direction(out, eigen_threads(1.0)) : IGAFD_OK;
 }
 
 igafd_status eigen_direction(Dir1D* out, int team_max) {

@@ -56,7 +56,7 @@ int main(int argc, char** argv) {
   };
   for (int threads : {2, 3, 5, 16})
     for (size_t k = 0; k < dirs.size() && all; ++k) same(solved(dirs[k], threads), k, "alone", threads);
-  const int threads = igafd::eigen_threads((int)dirs.size());
+  const int threads = igafd::eigen_threads(1.0 / (double)dirs.size());
   if (threads < 1 || threads * (int)dirs.size() > std::max(16, (int)dirs.size())) ++bad;
   std::vector<igafd::Dir1D> got(dirs);
   std::vector<std::thread> th;
