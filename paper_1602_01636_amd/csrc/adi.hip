@@ -197,10 +197,11 @@ __global__ __launch_bounds__(kLineBlock) void k_line_solve(const double* __restr
 //   D (dir 3): b = v + w s**; s = (K3 + w M3)^-1 M3 b; v = b - w s      4
 // Bound by latency: loads, product, two sweeps of a dependent chain over the line
 // and stores follow each other in a block, and 32 lines a block spread 97^2 lines
-// over all CUs once.  Measured at 97^3, p = 3: sub-steps 16, 20, 17 and 18 us (7 us
-// of it for moving the vectors, 2 for the tables, 2 for the product, 6 for the sweeps,
-// about 170 clocks per 4 rows each way), a step 72 us; the same step as ten launches
-// (five products, four solves, an update: 35 passes) took 219 us, most of it in solves
+// over all CUs once.  Measured at 97^3, p = 3 (launches that run; those behind the
+// stop flag end in 3 us): sub-steps A to D 17, 22, 18 and 20 us (about 7 of it for
+// moving the vectors, 2 for the tables, 2 for the product, 6 for the sweeps, about
+// 170 clocks per 4 rows each way), a step 78 us; the same step as ten launches
+// (five products, four solves, an update: 35 passes) took 247 us, most of it in solves
 // whose lines were loaded one value at a time.  Without the push form of the sweep
 // (four dependent multiply-adds a row, loads next to their use) a sub-step took 18
 // to 32 us; every load of a block in flight before the first wait did not pay (+1 us).

@@ -15,14 +15,14 @@
 // stored, and only the last, partial slice is zeroed beyond K.  (With a
 // choice between vector and edge loads inside the loop the compiler could not
 // count the loads in flight and waited for all of them on every slice: products of
-// 1027^3 in FP32 65-76 us, of the L-shaped domain's 515 x 1030 pairs in split BF16
-// 47-58 us, of 513^4 in FP64 3.35-3.57 ms; without 49-51, 30-33 and 3.0 ms.  Tiles
-// of 32 x 64 and 32 x 32, with more blocks in flight, moved these by -8 to +20 %.)
+// 1025^3 in FP32 65-78 us, of the L-shaped domain's 513 x 1027 pairs in split BF16
+// 54-67 us, of 513^4 in FP64 3.30-3.55 ms; without 48-53, 34-38 us and 2.87-2.91 ms.
+// Tiles of 32 x 64 and 32 x 32, with more blocks in flight, moved these by -8 to +20 %.)
 // Right operands of fewer columns than a thread loads at once (one to three, or
 // seven) run the same pipeline with their values loaded one by one: applies of
 // 3 x 1000 in FP64 / FP32 / BF16 / split BF16 113 / 75 / 63 / 72 us, slice by slice
 // without one in flight 138 / 118 / 118 / 137 us.
-// FP64 products are bound by the MFMA rate and its 12 % padding to 64 (53 TFLOP/s of
+// FP64 products are bound by the MFMA rate and its 12 % padding to 64 (54 TFLOP/s of
 // the 73 that a large library product reaches here); the 2D ones by the slice's chain
 // of loads, LDS and MFMAs at one or two blocks per CU.
 // Epilogue: division by lam_row[m] + lam_col[n], the diagonal scalings of
