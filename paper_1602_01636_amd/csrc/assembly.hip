@@ -47,12 +47,21 @@ struct RhsDesc {
 
 struct Tables {
   const int* first[3];
-  const int* at[3];  // at[l][f]: element whose first function is f, or -1 (f < n_l + 2)
   const double* qx[3];
   const double* qw[3];
   const double* val[3];
   const double* der[3];
   int n[3];
+};
+
+// The arguments of up to 216 launches in a row, which take as long as the host needs
+// for them: three pointers more made load vectors of 8^3 to 24^3 elements 4 %
+// slower (16^3, p = 3: 327 -> 339 us), so what only others need is not in here.
+static_assert(sizeof(Tables) == 15 * sizeof(void*) + 4 * sizeof(int), "argument of the element kernels");
+
+// for the kernels across the elements
+struct AcrossTables : Tables {
+  const int* at[3];  // at[l][f]: element whose first function is f, or -1 (f < n_l + 2)
 };
 
 template <int D>
@@ -562,7 +571,7 @@ constexpr int kFeat = 7;
 // itself, took 9.6 ms.
 template <int P>
 __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract3(
-    Tables T, GeomDesc g, Modes md, int nq1, int nq2, cidx_t* at, ctab_t* qx, ctab_t* qw, ctab_t* val,
+    AcrossTables T, GeomDesc g, Modes md, int nq1, int nq2, cidx_t* at, ctab_t* qx, ctab_t* qw, ctab_t* val,
     ctab_t* der, ctab_t* d3, int base, int end, int len, double* __restrict__ H,
     int* __restrict__ err) {
   extern __shared__ double sm[];
@@ -665,7 +674,7 @@ __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract3(
 // at 112^3, p = 4.
 template <int P, int NCH>
 __global__ __launch_bounds__(kCol) void k_moment3(
-    Tables T, GeomDesc g, Modes md, RhsDesc rhs, int nq1, int nq2, cidx_t* at, ctab_t* qx, ctab_t* qw,
+    AcrossTables T, GeomDesc g, Modes md, RhsDesc rhs, int nq1, int nq2, cidx_t* at, ctab_t* qx, ctab_t* qw,
     ctab_t* val, ctab_t* d3, int base, int end, int len, double* __restrict__ M1) {
   extern __shared__ double sm[];
   constexpr int Q = P + 1;
@@ -779,7 +788,7 @@ __device__ inline double wave_up1(double v) {
 // against 845 us per run of 72^3).
 template <int P>
 __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract12(
-    Tables T, cidx_t* at, ctab_t* val, ctab_t* der, const double* __restrict__ H, double* __restrict__ band, long long Ns, int nq1, int nq2, int base, int len1,
+    AcrossTables T, cidx_t* at, ctab_t* val, ctab_t* der, const double* __restrict__ H, double* __restrict__ band, long long Ns, int nq1, int nq2, int base, int len1,
     int len2) {
   extern __shared__ double sm[];
   using R = Run1<P>;
@@ -945,7 +954,7 @@ __global__ __launch_bounds__(2 * kCol, P <= 5 ? 2 : 1) void k_contract12(
 // Moments, direction 2: M2[i3][ch][i2][q1] from M1[i3][ch][q2][q1]; one thread
 // per (q1, channel plane y) and run of functions i2.
 template <int P>
-__global__ __launch_bounds__(kCol) void k_moment2(Tables T, cidx_t* at,
+__global__ __launch_bounds__(kCol) void k_moment2(AcrossTables T, cidx_t* at,
                                                   ctab_t* val, const double* __restrict__ M1,
                                                   double* __restrict__ M2, int nq1, int nq2, int len2) {
   constexpr int Q = P + 1;
@@ -977,7 +986,7 @@ __global__ __launch_bounds__(kCol) void k_moment2(Tables T, cidx_t* at,
 
 // sum_t w_t B_i(t) of direction l and function i (0-based interior index)
 template <int P>
-__device__ inline double moment1(const Tables& T, int l, int i) {
+__device__ inline double moment1(const AcrossTables& T, int l, int i) {
   constexpr int Q = P + 1;
   double s = 0.0;
 #pragma unroll
@@ -994,7 +1003,7 @@ __device__ inline double moment1(const Tables& T, int l, int i) {
 // b_i (NCH = 1), or the features feat_i = (M_ch / M_w, p) in FP32, the moment
 // of w a product of univariate ones.
 template <int P, int NCH, typename Out>
-__global__ __launch_bounds__(kBlock) void k_moment1(Tables T, const double* __restrict__ M2, int nq1, int base,
+__global__ __launch_bounds__(kBlock) void k_moment1(AcrossTables T, const double* __restrict__ M2, int nq1, int base,
                                                     int end, Out* __restrict__ out) {
   constexpr int Q = P + 1;
   const int n1 = T.n[0], n2 = T.n[1];
@@ -1290,13 +1299,19 @@ Tables make_tables(const igafd_ctx* c) {
   Tables T{};
   for (int l = 0; l < 3; ++l) {
     T.first[l] = c->ddir[l].elem_first;
-    T.at[l] = c->ddir[l].elem_at;
     T.qx[l] = c->ddir[l].qx;
     T.qw[l] = c->ddir[l].qw;
     T.val[l] = c->ddir[l].val;
     T.der[l] = c->ddir[l].der;
     T.n[l] = c->n[l];
   }
+  return T;
+}
+
+AcrossTables across_tables(const igafd_ctx* c) {
+  AcrossTables T{};
+  static_cast<Tables&>(T) = make_tables(c);
+  for (int l = 0; l < 3; ++l) T.at[l] = c->ddir[l].elem_at;
   return T;
 }
 
@@ -1326,7 +1341,7 @@ int column_run(int count, int colb) { return std::min(count, std::max(2, cdiv((l
 
 // moments of directions 2 and 1 for the planes [base, end): M1 -> M2 -> out
 template <int P, int NCH, typename Out>
-igafd_status moments21(igafd_ctx* c, const Tables& T, const double* M1, double* M2, int base, int end, Out* out) {
+igafd_status moments21(igafd_ctx* c, const AcrossTables& T, const double* M1, double* M2, int base, int end, Out* out) {
   const int nq1 = c->dir[0].nel * (P + 1), nq2 = c->dir[1].nel * (P + 1), n2 = c->n[1];
   const int planes = (end - base) * NCH, qb = cdiv(nq1, kCol);
   const int len2 = std::min(n2, std::max(4, cdiv(n2, cdiv(kAsmBlocks, (long long)qb * planes))));
@@ -1347,7 +1362,7 @@ template <int P>
 igafd_status launch_across(igafd_ctx* c, AsmWork* work) {
   using R = Run1<P>;
   constexpr int W = 2 * P + 1, NP3 = P + 1, NF = kFields3;
-  const Tables T = make_tables(c);
+  const AcrossTables T = across_tables(c);
   const int nq1 = c->dir[0].nel * R::Q, nq2 = c->dir[1].nel * R::Q;
   const int n2 = c->n[1], n3 = c->n[2];
   const long long nq12 = (long long)nq1 * nq2;
@@ -1413,7 +1428,7 @@ igafd_status launch_across(igafd_ctx* c, AsmWork* work) {
 template <int P>
 igafd_status load_across(igafd_ctx* c, RhsDesc rhs, double* b) {
   using R = Run1<P>;
-  const Tables T = make_tables(c);
+  const AcrossTables T = across_tables(c);
   const Modes md = modes_of(c);
   const int nq1 = c->dir[0].nel * R::Q, nq2 = c->dir[1].nel * R::Q, n2 = c->n[1], n3 = c->n[2];
   const int colb = cdiv((long long)nq1 * nq2, kCol);

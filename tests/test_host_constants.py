@@ -33,6 +33,8 @@ def _compiles(tmp_path, source, old=None, new=None):
     ("gemm.hip", "constexpr int kGap = 16;", "constexpr int kGap = 2;"),
     # a training block adds the gradient images of its two waves
     ("mlp.hip", "return train ? 2 : kBlock / 64;", "return train ? 4 : kBlock / 64;"),
+    # arguments of the element kernels' many small launches
+    ("assembly.hip", "  const double* der[3];\n  int n[3];", "  const double* der[3];\n  const int* at[3];\n  int n[3];"),
 ])
 def test_dependent_constants(tmp_path, source, old, new):
     ok, err = _compiles(tmp_path, source)
