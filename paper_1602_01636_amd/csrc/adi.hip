@@ -589,22 +589,24 @@ int lines_per_block(const igafd_ctx* c, int dir, int mode) {
   return 0;
 }
 
-// Dynamic LDS above 64 KB needs the kernel attribute; set once per problem at
-// setup (never inside a launch sequence that may be captured), to the largest size that
-// any problem's launch uses.
+// Dynamic LDS above 64 KB needs the kernel attribute; set at setup (never inside a
+// launch sequence that may be captured) for the sub-steps of this problem that use
+// more, to the largest size that any problem's launch uses.
 template <int P, int DIR, int MODE>
-igafd_status lds_attr1() {
+igafd_status lds_attr1(const igafd_ctx* c) {
+  const int lt = lines_per_block<P>(c, DIR, MODE);
+  if (lt == 0 || adi_lds<P>(MODE, lt, c->n[DIR]) <= 64 * 1024) return IGAFD_OK;
   for (const void* fn : {(const void*)&k_adi<P, DIR, 32, MODE>, (const void*)&k_adi<P, DIR, 16, MODE>})
     IGAFD_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAdiLds));
   return IGAFD_OK;
 }
 
 template <int P>
-igafd_status lds_attr() {
+igafd_status lds_attr(const igafd_ctx* c) {
   igafd_status s;
-  if ((s = lds_attr1<P, 1, ADI_INIT>()) != IGAFD_OK || (s = lds_attr1<P, 2, ADI_INIT>()) != IGAFD_OK ||
-      (s = lds_attr1<P, 1, ADI_A>()) != IGAFD_OK || (s = lds_attr1<P, 0, ADI_B>()) != IGAFD_OK ||
-      (s = lds_attr1<P, 1, ADI_C>()) != IGAFD_OK || (s = lds_attr1<P, 2, ADI_D>()) != IGAFD_OK)
+  if ((s = lds_attr1<P, 1, ADI_INIT>(c)) != IGAFD_OK || (s = lds_attr1<P, 2, ADI_INIT>(c)) != IGAFD_OK ||
+      (s = lds_attr1<P, 1, ADI_A>(c)) != IGAFD_OK || (s = lds_attr1<P, 0, ADI_B>(c)) != IGAFD_OK ||
+      (s = lds_attr1<P, 1, ADI_C>(c)) != IGAFD_OK || (s = lds_attr1<P, 2, ADI_D>(c)) != IGAFD_OK)
     return s;
   return IGAFD_OK;
 }
@@ -632,7 +634,7 @@ igafd_status adi_lds_attr(const igafd_ctx* c) {
   switch (c->p) {
 #define IGAFD_P(P) \
   case P:          \
-    return lds_attr<P>();
+    return lds_attr<P>(c);
     IGAFD_P(1) IGAFD_P(2) IGAFD_P(3) IGAFD_P(4) IGAFD_P(5) IGAFD_P(6)
 #undef IGAFD_P
     default:
@@ -795,13 +797,7 @@ int adi_dot_blocks(const igafd_ctx* c) {
 void adi_free(igafd_ctx* c) {
   igafd_adi* a = c->adi;
   if (!a) return;
-  for (int d = 0; d < 3; ++d) {
-    if (a->bandK[d]) (void)hipFree(a->bandK[d]);
-    if (a->bandM[d]) (void)hipFree(a->bandM[d]);
-    if (a->fac[d]) (void)hipFree(a->fac[d]);
-    if (a->rows[d]) (void)hipFree(a->rows[d]);
-  }
-  if (a->bandKw1) (void)hipFree(a->bandKw1);
+  if (a->tables) (void)hipFree(a->tables);
   if (a->work) (void)hipFree(a->work);
   delete a;
   c->adi = nullptr;
@@ -932,59 +928,55 @@ igafd_status adi_setup(igafd_ctx* c, double eps, int rule) {
     igafd_adi* a;
     ~Guard() {
       if (!a) return;
-      for (int d = 0; d < 3; ++d) {
-        if (a->bandK[d]) (void)hipFree(a->bandK[d]);
-        if (a->bandM[d]) (void)hipFree(a->bandM[d]);
-        if (a->fac[d]) (void)hipFree(a->fac[d]);
-        if (a->rows[d]) (void)hipFree(a->rows[d]);
-      }
-      if (a->bandKw1) (void)hipFree(a->bandKw1);
+      if (a->tables) (void)hipFree(a->tables);
       if (a->work) (void)hipFree(a->work);
     }
   } guard{st.get()};
+  // every table in one host array, each 256-byte aligned, for one allocation and one copy
+  std::vector<double> host;
+  std::vector<std::pair<const double**, size_t>> parts;  // the pointer of a table, its place
+  auto add = [&](const double** p, size_t count) {
+    parts.push_back({p, host.size()});
+    host.resize((host.size() + count + 31) / 32 * 32);
+    return host.data() + parts.back().second;  // until the next table is added
+  };
   for (int d = 0; d < 3; ++d) {
     const int n = c->dir[d].n;
     const std::vector<double> bK = band_of(c->dir[d].K, n, p), bM = band_of(c->dir[d].M, n, p);
-    std::vector<double> fac((size_t)(J + 1) * n * WL, 0.0);
-    bool ok = band_cholesky(bK, bM, 0.0, 1.0, n, p, fac.data());
-    for (int j = 0; j < J && ok; ++j) ok = band_cholesky(bK, bM, 1.0, w[j], n, p, fac.data() + (size_t)(j + 1) * n * WL);
+    std::copy(bK.begin(), bK.end(), add(&st->bandK[d], bK.size()));
+    std::copy(bM.begin(), bM.end(), add(&st->bandM[d], bM.size()));
+    const size_t slot = (size_t)n * WL;
+    double* fac = add(&st->fac[d], (J + 1) * slot);
+    bool ok = band_cholesky(bK, bM, 0.0, 1.0, n, p, fac);
+    for (int j = 0; j < J && ok; ++j) ok = band_cholesky(bK, bM, 1.0, w[j], n, p, fac + (j + 1) * slot);
     if (!ok) {
       set_error("band Cholesky of K_d + omega M_d failed");
       return IGAFD_ERR_NOT_SPD;
     }
-    IGAFD_HIP_CHECK(device_malloc((void**)&st->bandK[d], sizeof(double) * bK.size()));
-    IGAFD_HIP_CHECK(device_malloc((void**)&st->bandM[d], sizeof(double) * bM.size()));
     // the sweeps' rows (adi_sweep): forward 1/L_ii, L_{i+k,i}/L_{i+k,i+k}; backward, i from
     // the end after the zero rows, 1/L_ii, L_{i,i-k}/L_{i-k,i-k}
     const int RP = even_up(WL), R = adi_rows(n);
-    std::vector<double> rows((size_t)(J + 1) * 2 * R * RP, 0.0);
+    double* rows = add(&st->rows[d], (size_t)(J + 1) * 2 * R * RP);
+    fac = host.data() + parts[parts.size() - 2].second;
     for (int j = 0; j <= J; ++j)
       for (int i = 0; i < n; ++i) {
-        const double* f = fac.data() + (size_t)j * n * WL;
-        double* fw = rows.data() + ((size_t)j * 2 * R + i) * RP;
-        double* bw = rows.data() + ((size_t)j * 2 * R + R + (R - 1 - i)) * RP;
+        const double* f = fac + j * slot;
+        double* fw = rows + ((size_t)j * 2 * R + i) * RP;
+        double* bw = rows + ((size_t)j * 2 * R + R + (R - 1 - i)) * RP;
         fw[0] = bw[0] = f[(size_t)i * WL];
         for (int k = 1; k <= p; ++k) {
           if (i + k < n) fw[k] = f[(size_t)(i + k) * WL + k] * f[(size_t)(i + k) * WL];
           if (i - k >= 0) bw[k] = f[(size_t)i * WL + k] * f[(size_t)(i - k) * WL];
         }
       }
-    IGAFD_HIP_CHECK(device_malloc((void**)&st->rows[d], sizeof(double) * rows.size()));
-    IGAFD_HIP_CHECK(hipMemcpy(st->rows[d], rows.data(), sizeof(double) * rows.size(), hipMemcpyHostToDevice));
-    IGAFD_HIP_CHECK(device_malloc((void**)&st->fac[d], sizeof(double) * fac.size()));
-    IGAFD_HIP_CHECK(hipMemcpy(st->bandK[d], bK.data(), sizeof(double) * bK.size(), hipMemcpyHostToDevice));
-    IGAFD_HIP_CHECK(hipMemcpy(st->bandM[d], bM.data(), sizeof(double) * bM.size(), hipMemcpyHostToDevice));
-    IGAFD_HIP_CHECK(hipMemcpy(st->fac[d], fac.data(), sizeof(double) * fac.size(), hipMemcpyHostToDevice));
-  }
-  {  // K1 - omega_j M1 per parameter, direction 1
-    const int n = c->dir[0].n;
-    const std::vector<double> bK = band_of(c->dir[0].K, n, p), bM = band_of(c->dir[0].M, n, p);
-    std::vector<double> kw((size_t)J * n * W);
+    if (d > 0) continue;
+    double* kw = add(&st->bandKw1, (size_t)J * n * W);  // K1 - omega_j M1 per parameter
     for (int j = 0; j < J; ++j)
       for (size_t e = 0; e < bK.size(); ++e) kw[(size_t)j * n * W + e] = bK[e] - w[j] * bM[e];
-    IGAFD_HIP_CHECK(device_malloc((void**)&st->bandKw1, sizeof(double) * kw.size()));
-    IGAFD_HIP_CHECK(hipMemcpy(st->bandKw1, kw.data(), sizeof(double) * kw.size(), hipMemcpyHostToDevice));
   }
+  IGAFD_HIP_CHECK(device_malloc((void**)&st->tables, sizeof(double) * host.size()));
+  IGAFD_HIP_CHECK(hipMemcpy(st->tables, host.data(), sizeof(double) * host.size(), hipMemcpyHostToDevice));
+  for (const auto& part : parts) *part.first = st->tables + part.second;
   IGAFD_HIP_CHECK(device_malloc((void**)&st->work, sizeof(double) * 5 * (size_t)c->N));
   igafd_status sa = adi_lds_attr(c);
   if (sa != IGAFD_OK) return sa;

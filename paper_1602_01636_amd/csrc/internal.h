@@ -112,12 +112,13 @@ struct igafd_adi {
   int J0 = 0;
   // device: per direction the bands of K_d and M_d ([n][2p+1], entry (i, i+k-p))
   // and the lower band Cholesky factors ([n][p+1], entry (i, i-k)) of M_d
-  // (slot 0) and of K_d + omega_j M_d (slot j)
-  double* bandK[3] = {nullptr, nullptr, nullptr};
-  double* bandM[3] = {nullptr, nullptr, nullptr};
-  double* fac[3] = {nullptr, nullptr, nullptr};
-  double* rows[3] = {nullptr, nullptr, nullptr};  // the same by rows over the diagonal (k_adi): per slot forward, backward
-  double* bandKw1 = nullptr;  // K_1 - omega_j M_1 for every j: [J][n1][2p+1]
+  // (slot 0) and of K_d + omega_j M_d (slot j), all in one allocation
+  double* tables = nullptr;
+  const double* bandK[3] = {nullptr, nullptr, nullptr};
+  const double* bandM[3] = {nullptr, nullptr, nullptr};
+  const double* fac[3] = {nullptr, nullptr, nullptr};
+  const double* rows[3] = {nullptr, nullptr, nullptr};  // the same by rows over the diagonal (k_adi): per slot forward, backward
+  const double* bandKw1 = nullptr;  // K_1 - omega_j M_1 for every j: [J][n1][2p+1]
   double* work = nullptr;  // rt, v, u, t1, t2: 5 N doubles
 };
 

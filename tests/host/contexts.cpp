@@ -255,6 +255,30 @@ int adi_lines() {
   return 0;
 }
 
+// Switching to ADI takes one allocation for its tables and one for its vectors,
+// and raises the LDS limits of the sub-steps that need it only.
+int adi_setup() {
+  igafd_ctx* c = setup(20, 3, nullptr);
+  CHECK(c);
+  const size_t before = hip_double::live.size();
+  hip_double::forget();
+  int J = 0;
+  double rho = 0.0;
+  CHECK(igafd_set_adi(c, 0.1, &J, &rho) == IGAFD_OK && J > 1);
+  CHECK(hip_double::live.size() == before + 2);
+  CHECK(hip_double::attrs.empty());
+  CHECK(igafd_set_adi_greedy(c, 0.1, &J, &rho) == IGAFD_OK);  // the tables of the other rule go
+  CHECK(hip_double::live.size() == before + 2);
+  CHECK(igafd_set_adi(c, 0.0, &J, &rho) == IGAFD_OK && hip_double::live.size() == before);
+  igafd_destroy(c);
+  c = setup(95, 3, nullptr);
+  hip_double::forget();
+  CHECK(c && igafd_set_adi(c, 0.1, &J, &rho) == IGAFD_OK && !hip_double::attrs.empty());
+  CHECK(igafd_apply_precond(c, IGAFD_FP64, c->r, c->z) == IGAFD_OK && !hip_double::over_limit);
+  igafd_destroy(c);
+  return 0;
+}
+
 constexpr size_t kMiB = 1 << 20, kGiB = (size_t)1 << 30;
 
 void* take(size_t bytes) {
@@ -379,6 +403,7 @@ int main(int argc, char** argv) {
   if (what == "host_memory") bad = host_memory();
   if (what == "lds_limits") bad = lds_limits();
   if (what == "adi_lines") bad = adi_lines();
+  if (what == "adi_setup") bad = adi_setup();
   if (what == "cache_fit") bad = cache_fit();
   if (what == "cache_holds_all") bad = cache_holds_all();
   if (what == "cache_bound_and_age") bad = cache_bound_and_age();

@@ -62,3 +62,7 @@ def test_lds_limits_do_not_depend_on_the_problem(contexts):
 
 def test_adi_lines_by_the_device(contexts):
     _check(contexts, "adi_lines")
+
+
+def test_adi_setup_takes_two_allocations(contexts):
+    _check(contexts, "adi_setup")
