@@ -19,9 +19,9 @@
 // 54-67 us, of 513^4 in FP64 3.30-3.55 ms; without 48-53, 34-38 us and 2.87-2.91 ms.
 // Tiles of 32 x 64 and 32 x 32, with more blocks in flight, moved these by -8 to +20 %.)
 // Right operands of fewer columns than a thread loads at once (one to three, or
-// seven) run the same pipeline with their values loaded one by one: applies of
-// 3 x 1000 in FP64 / FP32 / BF16 / split BF16 113 / 75 / 63 / 72 us, slice by slice
-// without one in flight 138 / 118 / 118 / 137 us.
+// seven) run the same pipeline with their values loaded one by one, in kernels of
+// their own: applies of 3 x 1000 in FP64 / FP32 / BF16 / split BF16 114 / 78 / 62 /
+// 73 us, slice by slice without one in flight 138 / 118 / 118 / 137 us.
 // FP64 products are bound by the MFMA rate and its 12 % padding to 64 (54 TFLOP/s of
 // the 73 that a large library product reaches here); the 2D ones by the slice's chain
 // of loads, LDS and MFMAs at one or two blocks per CU.
@@ -194,8 +194,12 @@ __device__ inline void ldv(const T* p, V* o) {
   }
 }
 
-// PRE: A is scaled by ep.Sa (the input scaling of S P^-1 S)
-template <class G, int TM, int TN, bool BT, bool PRE, typename TA, typename TB, typename TC>
+// values that a thread loads of a slice of the right operand
+constexpr int slice_values(int tn) { return 2 * tn * 16 * kBK / kBlock; }
+
+// PRE: A is scaled by ep.Sa (the input scaling of S P^-1 S).  NARROW: the right
+// operand of an NN product may have fewer columns than a thread loads at once
+template <class G, int TM, int TN, bool BT, bool PRE, bool NARROW, typename TA, typename TB, typename TC>
 __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA, TB, TC> p1, int grid0) {
   // blocks [0, grid0) work on p0, the rest on p1 (uniform per block)
   const bool second = (int)blockIdx.x >= grid0;
@@ -214,7 +218,7 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   using acc_t = typename G::acc;
   constexpr int BM = 2 * TM * 16, BN = 2 * TN * 16, BK = kBK;
   constexpr int LA = BM + kPad, LB = BN + kPad;
-  constexpr int EA = BM * BK / kBlock, EB = BN * BK / kBlock;  // values per thread per slice
+  constexpr int EA = BM * BK / kBlock, EB = slice_values(TN);  // values per thread per slice
   constexpr int APR = BK / EA;                                 // threads per row of the A slice
   constexpr int BPR = BT ? BK / EB : BN / EB;                  // threads per row of the stored B slice
   // an edge tile of fewer than EB columns stores the copies of the columns left of
@@ -253,30 +257,27 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   const int bn0 = BT ? (bn < N ? bn : N - 1) : bn + EB <= N ? bn : N > EB ? N - EB : 0;
   const TB* brow = BT ? B + (long long)bn0 * ldb : B + (long long)br * ldb + bn0;
   const bool n_edge = !BT && tn0 + BN > N;
-  const bool narrow = !BT && N < EB;  // no EB columns to load as vectors
   const int bcl = BT ? bc : bc - (bn - bn0);  // NN: the columns' place (overlapping copies in an edge tile)
 
-  // the slices' registers must not reach memory: every piece is inlined
-#define IGAFD_INLINE_LAMBDA __attribute__((always_inline))
   struct Stage {
     V a[EA], b[EB];
     double s[PRE ? EA : 1];
   };
-  // full slice: runs of consecutive k (A, BT) or n (NN) as vectors (narrow B: value by
+  // full slice: runs of consecutive k (A, BT) or n (NN) as vectors (NARROW: value by
   // value), no conditions, so that waiting for one slice leaves the next one's loads in flight
-  auto load = [&](auto narrow_b, int k0, Stage& q) IGAFD_INLINE_LAMBDA {
+  auto load = [&](int k0, Stage& q) {
     ldv<EA>(arow + k0 + ak, q.a);
     if (PRE) ldv<EA>(srow + k0 + ak, q.s);
     if constexpr (BT)
       ldv<EB>(brow + k0 + bc, q.b);
-    else if constexpr (decltype(narrow_b)::value)
+    else if constexpr (NARROW)
 #pragma unroll
       for (int j = 0; j < EB; ++j) q.b[j] = (V)brow[(long long)k0 * ldb + (j < N ? j : N - 1)];
     else
       ldv<EB>(brow + (long long)k0 * ldb, q.b);
   };
   // the last slice, K % BK deep, value by value
-  auto load_tail = [&](int k0, Stage& q) IGAFD_INLINE_LAMBDA {
+  auto load_tail = [&](int k0, Stage& q) {
 #pragma unroll
     for (int j = 0; j < EA; ++j) {
       const int k = k0 + ak + j < K ? k0 + ak + j : K - 1;
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
     }
   };
   // write the slice to LDS; TAIL: zeros beyond K
-  auto store = [&](auto tail, int buf, int k0, const Stage& q) IGAFD_INLINE_LAMBDA {
+  auto store = [&](auto tail, int buf, int k0, const Stage& q) {
     constexpr bool TAIL = decltype(tail)::value;
     V* as = As + buf * SA;
     V* bs = Bs + buf * SB;
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
   const bool off = tm0 + wm0 >= M || tn0 + wn0 >= N;  // this wave's part lies outside the matrix
-  auto compute = [&](int buf) IGAFD_INLINE_LAMBDA {
+  auto compute = [&](int buf) {
     if (off) return;
     const V* as = As + buf * SA;
     const V* bs = Bs + buf * SB;
@@ -409,15 +410,15 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
   const std::integral_constant<bool, true> kTail;
   Stage q0, q1;
   // step t: load slice t+2 into stage t&1, compute slice t, store slice t+1
-  auto step = [&](auto narrow_b, int t, Stage& ql, const Stage& qs) IGAFD_INLINE_LAMBDA {
-    load(narrow_b, (t + 2) * BK, ql);
+  auto step = [&](int t, Stage& ql, const Stage& qs) {
+    load((t + 2) * BK, ql);
     __builtin_amdgcn_sched_barrier(0);  // issue the loads first
     compute(t & 1);
     store(kFull, (t + 1) & 1, (t + 1) * BK, qs);
     __syncthreads();
   };
   // the last two full slices and the tail; ql, qs as in step
-  auto finish = [&](int t, Stage& ql, const Stage& qs) IGAFD_INLINE_LAMBDA {  // t = nf - 2
+  auto finish = [&](int t, Stage& ql, const Stage& qs) {  // t = nf - 2
     if (tail) load_tail((t + 2) * BK, ql);
     compute(t & 1);
     store(kFull, (t + 1) & 1, (t + 1) * BK, qs);
@@ -429,44 +430,34 @@ __global__ __launch_bounds__(kBlock) void k_gemm(GProb<TA, TB, TC> p0, GProb<TA,
       compute(t & 1);
     }
   };
-  auto run = [&](auto narrow_b) IGAFD_INLINE_LAMBDA {
-    if (nf >= 2) {
-      load(narrow_b, 0, q0);
-      load(narrow_b, BK, q1);
-      store(kFull, 0, 0, q0);
-      __syncthreads();
-      int t = 0;
-      for (; t + 3 < nf; t += 2) {
-        step(narrow_b, t, q0, q1);
-        step(narrow_b, t + 1, q1, q0);
-      }
-      if (t + 2 < nf) {
-        step(narrow_b, t, q0, q1);
-        finish(t + 1, q1, q0);
-      } else {
-        finish(t, q0, q1);
-      }
-    } else {
-      if (nf == 1) {
-        load(narrow_b, 0, q0);
-        store(kFull, 0, 0, q0);
-      }
-      if (tail) {
-        load_tail(nf * BK, q1);
-        store(kTail, nf, nf * BK, q1);
-      }
-      __syncthreads();
-      if (nf == 1) compute(0);
-      if (tail) compute(nf);
+  if (nf >= 2) {
+    load(0, q0);
+    load(BK, q1);
+    store(kFull, 0, 0, q0);
+    __syncthreads();
+    int t = 0;
+    for (; t + 3 < nf; t += 2) {
+      step(t, q0, q1);
+      step(t + 1, q1, q0);
     }
-  };
-  if constexpr (BT) {
-    run(kFull);
+    if (t + 2 < nf) {
+      step(t, q0, q1);
+      finish(t + 1, q1, q0);
+    } else {
+      finish(t, q0, q1);
+    }
   } else {
-    if (narrow)
-      run(kTail);
-    else
-      run(kFull);
+    if (nf == 1) {
+      load(0, q0);
+      store(kFull, 0, 0, q0);
+    }
+    if (tail) {
+      load_tail(nf * BK, q1);
+      store(kTail, nf, nf * BK, q1);
+    }
+    __syncthreads();
+    if (nf == 1) compute(0);
+    if (tail) compute(nf);
   }
 
   double dot = 0.0;
@@ -552,7 +543,12 @@ igafd_status launch(hipStream_t st, GProb<TA, TB, TC> q0, const GProb<TA, TB, TC
     set_error("internal: paired products are not batched");
     return IGAFD_ERR_ARG;
   }
-  const Cfg g = q1 ? pick(q0.M, q0.N, q1->M, q1->N) : pick(q0.M, q0.N, 0, 0, q0.batch);
+  Cfg g = q1 ? pick(q0.M, q0.N, q1->M, q1->N) : pick(q0.M, q0.N, 0, 0, q0.batch);
+  // a kernel of its own, in one tile shape, where a right operand is too narrow for
+  // whole loads: in the others the choice would cost registers (FP64 128 -> 131, a
+  // wave per SIMD; 513^4 products 0.6 % slower)
+  const bool narrow = !BT && std::min(q0.N, q1 ? q1->N : q0.N) < slice_values(g.tn);
+  if (narrow) g = {2, 2};
   auto shape = [&](GProb<TA, TB, TC>& q) {
     q.tiles_n = (q.N + 32 * g.tn - 1) / (32 * g.tn);
     q.tiles_b = ((q.M + 32 * g.tm - 1) / (32 * g.tm)) * q.tiles_n;
@@ -568,21 +564,32 @@ igafd_status launch(hipStream_t st, GProb<TA, TB, TC> q0, const GProb<TA, TB, TC
   }
   const int grid0 = grid_of(q0.M, q0.N, g, q0.batch);
   const dim3 grid((unsigned)grid_all);
-#define IGAFD_G(TM, TN)                                                                                         \
-  if (g.tm == TM && g.tn == TN) {                                                                               \
-    constexpr size_t lds = lds_bytes<TM, TN, V>();                                                              \
-    if (lds > 64 * 1024) {                                                                                      \
-      static const hipError_t e0 = lds_attr(k_gemm<G, TM, TN, BT, false, TA, TB, TC>, lds);                    \
-      static const hipError_t e1 = lds_attr(k_gemm<G, TM, TN, BT, true, TA, TB, TC>, lds);                     \
-      IGAFD_HIP_CHECK(e0);                                                                                      \
-      IGAFD_HIP_CHECK(e1);                                                                                      \
-    }                                                                                                           \
-    if (q0.ep.Sa || p1.ep.Sa)                                                                                   \
-      hipLaunchKernelGGL((k_gemm<G, TM, TN, BT, true, TA, TB, TC>), grid, dim3(kBlock), lds, st, q0, p1, grid0); \
-    else                                                                                                        \
-      hipLaunchKernelGGL((k_gemm<G, TM, TN, BT, false, TA, TB, TC>), grid, dim3(kBlock), lds, st, q0, p1, grid0); \
-    IGAFD_HIP_CHECK(hipGetLastError());                                                                         \
-    return IGAFD_OK;                                                                                            \
+  const dim3 block(kBlock);
+  if constexpr (!BT)
+    if (narrow) {
+      constexpr size_t lds = lds_bytes<2, 2, V>();
+      if (q0.ep.Sa || p1.ep.Sa)
+        hipLaunchKernelGGL((k_gemm<G, 2, 2, BT, true, true, TA, TB, TC>), grid, block, lds, st, q0, p1, grid0);
+      else
+        hipLaunchKernelGGL((k_gemm<G, 2, 2, BT, false, true, TA, TB, TC>), grid, block, lds, st, q0, p1, grid0);
+      IGAFD_HIP_CHECK(hipGetLastError());
+      return IGAFD_OK;
+    }
+#define IGAFD_G(TM, TN)                                                                                            \
+  if (g.tm == TM && g.tn == TN) {                                                                                  \
+    constexpr size_t lds = lds_bytes<TM, TN, V>();                                                                 \
+    if (lds > 64 * 1024) {                                                                                         \
+      static const hipError_t e0 = lds_attr(k_gemm<G, TM, TN, BT, false, false, TA, TB, TC>, lds);                 \
+      static const hipError_t e1 = lds_attr(k_gemm<G, TM, TN, BT, true, false, TA, TB, TC>, lds);                  \
+      IGAFD_HIP_CHECK(e0);                                                                                         \
+      IGAFD_HIP_CHECK(e1);                                                                                         \
+    }                                                                                                              \
+    if (q0.ep.Sa || p1.ep.Sa)                                                                                      \
+      hipLaunchKernelGGL((k_gemm<G, TM, TN, BT, true, false, TA, TB, TC>), grid, block, lds, st, q0, p1, grid0);   \
+    else                                                                                                           \
+      hipLaunchKernelGGL((k_gemm<G, TM, TN, BT, false, false, TA, TB, TC>), grid, block, lds, st, q0, p1, grid0);  \
+    IGAFD_HIP_CHECK(hipGetLastError());                                                                            \
+    return IGAFD_OK;                                                                                               \
   }
   IGAFD_G(4, 4) IGAFD_G(4, 2) IGAFD_G(2, 4) IGAFD_G(2, 2)
 #undef IGAFD_G
