@@ -687,7 +687,11 @@ igafd_status spmv_set_tile(igafd_ctx* c, int b2, int b3, int tb) {
     c->ext = nullptr;
     c->ext_cap = 0;
     const igafd_status s = block_alloc((void**)&c->ext, sizeof(double) * (size_t)need);
-    if (s != IGAFD_OK) return s;
+    if (s != IGAFD_OK) {  // the shape in use has lost its buffer too
+      c->tile_b2 = c->tile_b3 = 0;
+      c->tile_tb = 256;
+      return s;
+    }
     c->ext_cap = need;
   }
   c->tile_b2 = b2;

@@ -279,6 +279,26 @@ int adi_setup() {
   return 0;
 }
 
+// A tile shape whose accumulators find no room leaves the context with the
+// row-parallel A product, not with the old shape and no accumulators.
+int tile_without_room() {
+  igafd_ctx* c = setup(64, 3, nullptr);
+  CHECK(c && c->tile_b2 > 0 && c->ext);
+  const int b2 = c->tile_b2, b3 = c->tile_b3, tb = c->tile_tb;
+  const size_t held = hip_double::bytes_on(0);
+  igafd::block_free(c->ext, false);  // as a larger shape does before it asks
+  c->ext = nullptr;
+  c->ext_cap = 0;
+  hip_double::capacity = hip_double::bytes_on(0) + 1000;
+  CHECK(igafd::spmv_set_tile(c, b2, b3, tb) != IGAFD_OK);
+  CHECK(c->tile_b2 == 0 && !c->ext);
+  CHECK(igafd_apply_A(c, c->r, c->z) == IGAFD_OK);
+  hip_double::capacity = held + (64 << 20);
+  CHECK(igafd::spmv_set_tile(c, b2, b3, tb) == IGAFD_OK && c->ext && c->tile_b2 == b2);
+  igafd_destroy(c);
+  return 0;
+}
+
 constexpr size_t kMiB = 1 << 20, kGiB = (size_t)1 << 30;
 
 void* take(size_t bytes) {
@@ -404,6 +424,7 @@ int main(int argc, char** argv) {
   if (what == "lds_limits") bad = lds_limits();
   if (what == "adi_lines") bad = adi_lines();
   if (what == "adi_setup") bad = adi_setup();
+  if (what == "tile_without_room") bad = tile_without_room();
   if (what == "cache_fit") bad = cache_fit();
   if (what == "cache_holds_all") bad = cache_holds_all();
   if (what == "cache_bound_and_age") bad = cache_bound_and_age();

@@ -66,3 +66,7 @@ def test_adi_lines_by_the_device(contexts):
 
 def test_adi_setup_takes_two_allocations(contexts):
     _check(contexts, "adi_setup")
+
+
+def test_tile_shape_without_room(contexts):
+    _check(contexts, "tile_without_room")
