@@ -162,7 +162,10 @@ igafd_status block_alloc(void** p, size_t bytes) {
 bool wait_stream(hipStream_t stream, int device) {
   int current = device;
   (void)hipGetDevice(&current);
-  if (current != device && hipSetDevice(device) != hipSuccess) return false;
+  if (current != device && hipSetDevice(device) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
   hipError_t e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
     e = hipDeviceSynchronize();

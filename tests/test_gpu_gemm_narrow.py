@@ -56,3 +56,23 @@ def test_narrow_takes_no_longer_than_wider(api, prec):
 
     narrow, wider = us(3), us(5)
     assert narrow < 1.25 * wider, (narrow, wider)
+
+
+@pytest.mark.parametrize("E", [2, 3, 4, 5, 9])
+def test_narrow_in_a_pair(api, E, monkeypatch):
+    """The L-shaped domain's two subdomains, h x (2h + 1) and (2h + 1) x h with
+    h = E - 1, share their launches: a narrow product beside one that is not."""
+    from oracle import multipatch as mp
+    monkeypatch.setenv("IGAFD_FD_GEMM", "1")
+    knots = synth.uniform_knots(E, 1)
+    L = mp.LShape(knots, 1)
+    S = mp.Schwarz(L)
+    pos, n = L.square_index()
+    r = np.zeros(n * n)
+    r[pos] = synth.random_vector(L.N, 5)
+    ref = S.ias(r[pos])
+    with api.igafd_lshape_setup(knots, 1) as ctx:
+        for prec, tol in (("fp64", 1e-11), ("fp32", 1e-4), ("bf16", 5e-2), ("bf16x3", 6e-4)):
+            s = to_dev(np.full(n * n, np.nan))
+            api.igafd_apply_precond(ctx, prec, to_dev(r), s)
+            assert rel(to_host(s)[pos], ref) < tol, prec
