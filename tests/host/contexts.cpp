@@ -299,6 +299,43 @@ int tile_without_room() {
   return 0;
 }
 
+// Each device allocation of a sequence of calls fails in turn (and the second
+// try with it): a status, no use of what is not there, and nothing left behind.
+int device_memory() {
+  const std::vector<double> k = knots(30, 3);
+  for (long long f = 0;; ++f) {
+    hip_double::device_allocs = 0;
+    hip_double::fail_alloc = f;
+    igafd_ctx* c = setup(30, 3, nullptr, true);
+    igafd_ctx* d = nullptr;
+    (void)igafd_lshape_setup(3, (int)k.size(), k.data(), nullptr, &d);
+    if (c) {
+      double* x = c->r;
+      (void)igafd_set_scaling(c, x);
+      (void)igafd_set_scaling_diag_ratio(c);
+      int J = 0;
+      (void)igafd_set_adi_greedy(c, 0.1, &J, nullptr);
+      (void)igafd_apply_precond(c, IGAFD_FP64, c->r, c->z);
+      (void)igafd_set_adi(c, 0.0, nullptr, nullptr);
+      (void)igafd_autotune(c, 0, 0);
+      CHECK(c->tile_b2 == 0 || c->ext);
+      (void)igafd_apply_A(c, c->q, c->z);
+      (void)igafd_load_vector(c, IGAFD_RHS_ONE, nullptr, 0, c->q);
+    }
+    igafd_destroy(c);
+    igafd_destroy(d);
+    const bool hit = hip_double::device_allocs > f;
+    hip_double::fail_alloc = -1;
+    igafd_release_cached();
+    CHECK(hip_double::live.empty());
+    (void)hipGetLastError();
+    if (!hit) {
+      std::printf("%lld device allocations\n", hip_double::device_allocs);
+      return 0;
+    }
+  }
+}
+
 constexpr size_t kMiB = 1 << 20, kGiB = (size_t)1 << 30;
 
 void* take(size_t bytes) {
@@ -425,6 +462,7 @@ int main(int argc, char** argv) {
   if (what == "adi_lines") bad = adi_lines();
   if (what == "adi_setup") bad = adi_setup();
   if (what == "tile_without_room") bad = tile_without_room();
+  if (what == "device_memory") bad = device_memory();
   if (what == "cache_fit") bad = cache_fit();
   if (what == "cache_holds_all") bad = cache_holds_all();
   if (what == "cache_bound_and_age") bad = cache_bound_and_age();

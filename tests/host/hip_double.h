@@ -52,6 +52,7 @@ inline long long large_mallocs = 0, frees = 0;  // of 1 MiB and more; all
 inline std::vector<Sync> syncs;
 inline std::vector<Attr> attrs;        // hipFuncSetAttribute, dynamic LDS
 inline int cus = 256;
+inline long long device_allocs = 0, fail_alloc = -1;  // with fail_alloc >= 0, that one and the next fail
 inline bool over_limit = false;        // a launch asked for more dynamic LDS than its function's limit
 inline hipStream_t dead = nullptr;     // a stream that was destroyed: waiting for it fails
 inline bool device_lost = false;       // waiting for the device fails too
@@ -113,6 +114,8 @@ hipError_t hipGetLastError(void) {
 hipError_t hipMalloc(void** p, size_t bytes) {
   Locked lock;
   *p = nullptr;
+  const long long k = device_allocs++;
+  if (fail_alloc >= 0 && (k == fail_alloc || k == fail_alloc + 1)) return done(hipErrorOutOfMemory);
   if (used[device] + bytes > capacity) return done(hipErrorOutOfMemory);
   void* m = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
   if (m == MAP_FAILED) return done(hipErrorOutOfMemory);

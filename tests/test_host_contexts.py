@@ -70,3 +70,7 @@ def test_adi_setup_takes_two_allocations(contexts):
 
 def test_tile_shape_without_room(contexts):
     _check(contexts, "tile_without_room")
+
+
+def test_out_of_device_memory_is_a_status(contexts):
+    _check(contexts, "device_memory")
