@@ -21,6 +21,8 @@ def _run(tmp_path, flags, args, **kw):
     res = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stderr[-3000:]
     res = subprocess.run([exe, *args], capture_output=True, text=True, timeout=600, **kw)
+    if "unexpected memory mapping" in res.stderr:
+        pytest.skip("the sanitizer's runtime does not start under this kernel's address layout")
     assert res.returncode == 0 and res.stdout.strip().endswith("OK"), res.stdout[-2000:] + res.stderr[-4000:]
 
 
